@@ -41,6 +41,12 @@ HD float bf16_to_float(bf16_t h) {
 }
 
 HD bf16_t float_to_bf16(float f) {  // round to nearest even (NaN kept quiet)
+#ifdef __HIP_DEVICE_COMPILE__  // the conversion instruction: the same rounding, one operation for two values
+  bf16_t d;
+  const __bf16 b = (__bf16)f;
+  __builtin_memcpy(&d.v, &b, 2);
+  return d;
+#endif
   uint32_t u;
   __builtin_memcpy(&u, &f, 4);
   bf16_t r;
@@ -241,6 +247,67 @@ HD int brick_site(const Geo& g, int p) {
   br /= nby;
   const int iz = br % nbz, it = br / nbz;
   return (((it * bt + rt) * g.Z + iz * bz + rz) * g.Y + iy * by + ry) * g.Xh + ix * bxh + rx;
+}
+
+// Position of a wave's sweep: brick origin and position inside the brick (the order of
+// brick_site<true>: y fastest, then x, z, t, bricks in lexicographic order).  Stepped by carries:
+// finding each position with integer divisions took half of the ~470 instructions a (site, tile) item
+// issued, and a wave issues one instruction every four to five cycles whatever else the chip does.
+struct SweepCursor {
+  int X0, Y0, Z0, T0, rx, ry, rz, rt;
+  HD void init(const Geo& g, int p) {
+    const int B = g.bxh * g.by * g.bz * g.bt;
+    int br = p / B, r = p - br * B;
+    ry = r % g.by;
+    r /= g.by;
+    rx = r % g.bxh;
+    r /= g.bxh;
+    rz = r % g.bz;
+    rt = r / g.bz;
+    const int nbx = g.Xh / g.bxh, nby = g.Y / g.by, nbz = g.Z / g.bz;
+    X0 = (br % nbx) * g.bxh;
+    br /= nbx;
+    Y0 = (br % nby) * g.by;
+    br /= nby;
+    Z0 = (br % nbz) * g.bz;
+    T0 = br / nbz * g.bt;
+  }
+  HD void next(const Geo& g) {
+    if (++ry < g.by) return;
+    ry = 0;
+    if (++rx < g.bxh) return;
+    rx = 0;
+    if (++rz < g.bz) return;
+    rz = 0;
+    if (++rt < g.bt) return;
+    rt = 0;
+    if ((X0 += g.bxh) < g.Xh) return;
+    X0 = 0;
+    if ((Y0 += g.by) < g.Y) return;
+    Y0 = 0;
+    if ((Z0 += g.bz) < g.Z) return;
+    Z0 = 0;
+    T0 += g.bt;
+  }
+};
+
+// cb indices of the eight neighbours (d = 2 mu + f, f = 0 forward, 1 backward) of the cursor's site of
+// parity par; returns the site's own
+HD int cursor_neighbours(const Geo& g, const SweepCursor& c, int par, int nb[8]) {
+  const int xh = c.X0 + c.rx, y = c.Y0 + c.ry, z = c.Z0 + c.rz, t = c.T0 + c.rt;
+  const int sy = g.Xh, sz = g.Xh * g.Y, st = g.Xh * g.Y * g.Z;
+  const int site = t * st + z * sz + y * sy + xh;
+  const int x = 2 * xh + ((y + z + t + par) & 1);
+  const int row = site - xh;
+  nb[0] = row + ((x + 1 == g.X ? 0 : x + 1) >> 1);
+  nb[1] = row + ((x == 0 ? g.X - 1 : x - 1) >> 1);
+  nb[2] = site + (y == g.Y - 1 ? sy - sz : sy);
+  nb[3] = site + (y == 0 ? sz - sy : -sy);
+  nb[4] = site + (z == g.Z - 1 ? sz - st : sz);
+  nb[5] = site + (z == 0 ? st - sz : -sz);
+  nb[6] = site + (t == g.T - 1 ? st - g.hv : st);
+  nb[7] = site + (t == 0 ? g.hv - st : -st);
+  return site;
 }
 
 HD void cb_coords(const Geo& g, int cb, int par, int c[4]) {
@@ -449,6 +516,8 @@ HD void clover_apply_mem(const void* base, long hv, long site, const Spinor<A>& 
 // Index 0 of each [2] is the inner (working) precision, index 1 is FP64.
 struct OpDev {
   Geo g;
+  int nsub;  // blocks per BS sites of the interleaved kernels' launches (a power of two <= 16)
+  int pad;
   double kappa;
   const void* U[2][2];   // [prec][parity] -> 4 link fields (mu-major) of that parity's sites
   const void* A[2][2];   // [prec][parity] clover
@@ -472,7 +541,7 @@ struct SlotDev {
   int op;
   int nblk;              // site blocks of this slot's operator
   int sid;               // stable slot id: index of its reduction partials and counter
-  int pad;
+  int il;                // 1: in a lane-interleaved group
   char* arena[2];        // [prec] base of this slot's vectors
   long long vstride[2];  // [prec] bytes between consecutive vectors
   long long lss, lcs;    // inner vectors: bytes between sites, between chunks of a site

@@ -56,7 +56,7 @@ struct HopMArgs {
   double ca, cb, gsign;
   int gpow;
   int red;
-  int nt3;  // every group of the launch has three lane tiles (48-lane groups)
+  int nt;  // lane tiles of every group of the launch
   RedBuf rb;
 };
 
@@ -109,8 +109,18 @@ struct LayoutArgs {
 // Sum the block partials of `kind` for n slots (slot table indices from `list`, or 0..n-1
 // when list is null) in block order and apply the scalar update.  Must follow the reducing
 // launch on the same stream.
-void launch_finalize(int kind, const OpDev* ops, const SlotDev* slots, const int* list, int n, RedBuf rb,
+// from: the kernels that stored the partials of slots in interleaved groups (others: FIN_SLOT always).
+enum FinFrom {
+  FIN_SLOT = 0,  // per-slot kernels: one partial per BS sites
+  FIN_MFMA,      // the matrix-core stencil: nsub partials per BS sites
+  FIN_VEC_IL,    // the interleaved vector kernels: min(nsub, VEC_IL_SUB) per BS sites
+};
+constexpr int VEC_IL_SUB = 4;
+void launch_finalize(int kind, int from, const OpDev* ops, const SlotDev* slots, const int* list, int n, RedBuf rb,
                      hipStream_t s);
+// Blocks per BS sites of the interleaved kernels, by the lattice alone (so that a source's result does
+// not depend on what shares its launches).
+int il_subblocks(int hv);
 
 void launch_hop(int prec, int R, const HopArgs& a, int ntiles, hipStream_t s);
 // the FP64 correction-form variants (HopArgs::lo_mask): first stencil EPI_INV with the hopping

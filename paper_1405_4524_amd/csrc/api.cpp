@@ -112,9 +112,13 @@ int il_alloc(Ctx* c, Slot* slots, int n, long hv, int nlo, int width) {
 
 // arenas of n slots of one operator: per slot, or interleaved groups for FP16 / BF16.  Whole
 // 16-lane tiles go to interleaved groups; a remainder of at least IL_REM_MIN sources gets a
-// tile of its own, a smaller one stays per slot (a tile costs the same whatever its fill: the
-// per-thread stencil is cheaper per RHS below about 12 of 16 lanes).
-constexpr int IL_REM_MIN = 12;
+// tile of its own, a smaller one stays per slot: a tile costs the same whatever its fill, and the
+// per-thread stencil is cheaper per RHS below that (32^3x64: 1550 us for a tile, 1880 for 12 per-thread
+// sources; 16^3x32: 89 us for one more tile, 117 for 12).  Beside whole tiles on a lattice where
+// launches cost more than the work (IL_REM_HV), any remainder joins them (8^3x16, 16 + 4 sources: the
+// second tile adds 3 us to the pair, four per-slot sources 19 us and their own vector launches).
+constexpr int IL_REM_MIN = 9;
+constexpr long IL_REM_HV = 1L << 15;
 
 // ilw: RHS per interleaved group (16, 32 or 48; 0 = the context's option)
 int slots_alloc(Ctx* c, Slot* slots, int n, int prec, long hv, int nblk, int nlo, int nhi, int ilw = 0) {
@@ -124,7 +128,7 @@ int slots_alloc(Ctx* c, Slot* slots, int n, int prec, long hv, int nblk, int nlo
   int n_il = 0;
   if (il) {
     n_il = n / 16 * 16;
-    if (n - n_il >= IL_REM_MIN) n_il = n;
+    if (n - n_il >= IL_REM_MIN || (n_il > 0 && hv <= IL_REM_HV)) n_il = n;
   }
   int rc = A2A_OK;
   int k = 0;
@@ -135,9 +139,9 @@ int slots_alloc(Ctx* c, Slot* slots, int n, int prec, long hv, int nblk, int nlo
   return rc;
 }
 
+// RHS per thread of the per-thread stencil: the option's, 0 = the solver's choice
 int effective_R(Ctx* c, int prec) {
   int R = c->rhs_block;
-  if (R != 1 && R != 2 && R != 4) R = 1;
   if (prec == 0 && R > 2) R = 2;
   return R;
 }
@@ -217,7 +221,7 @@ static int solve_batch(Ctx* c, int clover_h, const double* src, int nrhs, double
   if (c->autotune) A2A_TRY(autotune_cfg(c, clover_h, kappa, prec, nrhs, &tc, nullptr));
   const int R = tc.R ? tc.R : effective_R(c, prec);
   Solver sv(c, prec, R);
-  if (tc.R64) sv.R64 = tc.R64;
+  if (tc.R64) sv.set_R64(tc.R64);
   if (tc.slab >= 0) sv.mfma_slab = tc.slab;
   if (tc.by > 0) {
     sv.by = tc.by;
@@ -243,7 +247,7 @@ static int solve_batch(Ctx* c, int clover_h, const double* src, int nrhs, double
     s.max_iter = max_iter;
     s.t_submit = t0;
   }
-  rc = slots_alloc(c, slots.data(), nrhs, prec, hv, sv.ops[op].nblk, NVEC_LO, NVEC_HI, tc.il_width);
+  rc = slots_alloc(c, slots.data(), nrhs, prec, hv, sv.ops[op].partials(), NVEC_LO, NVEC_HI, tc.il_width);
   if (!rc) {
     std::vector<int> idx;
     for (int i = 0; i < nrhs; ++i) {
@@ -326,7 +330,7 @@ int dslash_core(Ctx* c, int clover_h, double kappa, int opk, int dagger, int pre
     s.src = in + (size_t)i * 24 * V;
     s.sol = out + (size_t)i * 24 * V;
   }
-  rc = slots_alloc(c, slots.data(), nrhs, prec, hv, sv.ops[op].nblk, 5, 0);
+  rc = slots_alloc(c, slots.data(), nrhs, prec, hv, sv.ops[op].partials(), 5, 0);
   if (!rc)
     for (auto& s : slots) sv.add_slot(&s);
   if (!rc) rc = sv.rebuild();
@@ -785,7 +789,7 @@ static int stencil_time(Ctx* c, int clover_h, double kappa, int opk, int prec, i
   std::vector<Slot> slots(nrhs);
   int rc = A2A_OK;
   for (int i = 0; i < nrhs; ++i) slots[i].op = op;
-  rc = slots_alloc(c, slots.data(), nrhs, prec, gf->g.hv, sv.ops[op].nblk, 5, 0, tc.il_width);
+  rc = slots_alloc(c, slots.data(), nrhs, prec, gf->g.hv, sv.ops[op].partials(), 5, 0, tc.il_width);
   if (!rc)
     for (auto& s : slots) sv.add_slot(&s);
   if (!rc) rc = sv.rebuild();
@@ -831,7 +835,7 @@ static int ru_time(Ctx* c, int clover_h, double kappa, int prec, int nrhs, int r
   KappaOp* kop;
   A2A_TRY(resolve_op(c, clover_h, kappa, prec, &gf, &cf, &kop));
   Solver sv(c, prec, il.R ? il.R : effective_R(c, prec));
-  sv.R64 = f64.R;
+  sv.set_R64(f64.R);
   if (il.by > 0) {
     sv.by = il.by;
     sv.bz = il.bz;
@@ -845,7 +849,7 @@ static int ru_time(Ctx* c, int clover_h, double kappa, int prec, int nrhs, int r
   std::vector<Slot> slots(nrhs);
   int rc = A2A_OK;
   for (int i = 0; i < nrhs; ++i) slots[i].op = op;
-  rc = slots_alloc(c, slots.data(), nrhs, prec, gf->g.hv, sv.ops[op].nblk, NVEC_LO, NVEC_HI, il.il_width);
+  rc = slots_alloc(c, slots.data(), nrhs, prec, gf->g.hv, sv.ops[op].partials(), NVEC_LO, NVEC_HI, il.il_width);
   if (!rc)
     for (auto& s : slots) sv.add_slot(&s);
   if (!rc) rc = sv.rebuild();
@@ -1782,7 +1786,7 @@ static int engine_admit(a2a_engine* e, Request* r) {
     s.req = r->ticket;
     s.req_idx = i;
   }
-  rc = slots_alloc(c, r->slots.data(), r->nsrc, r->prec, gf->g.hv, sv->ops[op].nblk, NVEC_LO, NVEC_HI);
+  rc = slots_alloc(c, r->slots.data(), r->nsrc, r->prec, gf->g.hv, sv->ops[op].partials(), NVEC_LO, NVEC_HI);
   if (rc) {
     r->slots.clear();
     return rc;

@@ -255,14 +255,15 @@ __global__ __launch_bounds__(BS) void k_vec(VecArgs a) {
   }
 }
 
-// interleaved mapping: tiles {16-lane group tile, block of BS sites}; BSI threads as (lane n,
-// row q) visit sites block*BS + 64 i + q, and a block keeps 16 waves of loads in flight.
+// interleaved mapping: tiles {16-lane group tile, block of sb = BS / min(nsub, VEC_IL_SUB) sites}; BSI
+// threads as (lane n, row q) visit sites block*sb + 64 i + q, and a block keeps 16 waves of loads in
+// flight.
 // Kinds on inner vectors only give a wave 4 sites x 16 lanes (4 contiguous 256-byte runs per
 // chunk).  Kinds that also touch the slots' FP64 vectors, whose chunk planes are per slot
 // ([chunk][site]), give a wave 8 sites x 8 lanes instead: 8 full 128-byte lines of the
 // interleaved arena per chunk, and for each of its 8 slots 8 consecutive FP64 chunks = one full
 // line (4 sites x 16 lanes used half lines there).  Reductions are per lane (slot) and land in
-// the same partial slots as the per-slot mapping (block index = site block of BS sites).
+// the partial slots of the tile's block index.
 constexpr int BSI = 1024;
 
 template <int KIND>
@@ -283,11 +284,13 @@ __global__ __launch_bounds__(BSI) void k_vec_il(VecArgs a) {
   double v3[3] = {0.0, 0.0, 0.0};
   if (slot >= 0) {
     const SlotDev& sd = a.slots[slot];
-    const int hv = a.ops[sd.op].g.hv;
+    const OpDev& op = a.ops[sd.op];
+    const int hv = op.g.hv;
+    const int sb = BS / min(op.nsub, VEC_IL_SUB);  // sites of this block
 #pragma unroll
     for (int i = 0; i < BS / (BSI / 16); ++i) {
-      const int site = tile.y * BS + (BSI / 16) * i + q;
-      if (site < hv) vec_site<P, KIND, true>(a, sd, hv, site, v3);
+      const int site = tile.y * sb + (BSI / 16) * i + q;
+      if ((BSI / 16) * i < sb && site < hv) vec_site<P, KIND, true>(a, sd, hv, site, v3);
     }
   }
   if (VecRed<KIND>::on) {
@@ -396,13 +399,15 @@ void launch_vec(int prec, const VecArgs& a, int ntiles, hipStream_t s) {
 // ------------------------------------------------------------------------------------
 // reduction finalize: one 64-thread block per slot, partials summed in block order
 // ------------------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void k_finalize(int kind, const OpDev* ops, const SlotDev* slots, const int* list,
-                                                  RedBuf rb) {
+__global__ __launch_bounds__(64) void k_finalize(int kind, int from, const OpDev* ops, const SlotDev* slots,
+                                                  const int* list, RedBuf rb) {
   const int idx = list ? list[blockIdx.x] : (int)blockIdx.x;
   const SlotDev& sd = slots[idx];
   const double* p = rb.partials + (size_t)sd.sid * rb.maxblk * RED_NV;
   double v[RED_NV] = {0.0, 0.0, 0.0};
-  for (int b = threadIdx.x; b < sd.nblk; b += 64)
+  const int nsub = ops[sd.op].nsub;
+  const int nblk = sd.nblk * (!sd.il || from == FIN_SLOT ? 1 : from == FIN_MFMA ? nsub : min(nsub, VEC_IL_SUB));
+  for (int b = threadIdx.x; b < nblk; b += 64)
 #pragma unroll
     for (int k = 0; k < RED_NV; ++k) v[k] += p[(size_t)b * RED_NV + k];
 #pragma unroll
@@ -410,10 +415,10 @@ __global__ __launch_bounds__(64) void k_finalize(int kind, const OpDev* ops, con
   if (threadIdx.x == 0) finalize_slot(kind, sd.scal, v, ops[sd.op].g.hv);
 }
 
-void launch_finalize(int kind, const OpDev* ops, const SlotDev* slots, const int* list, int n, RedBuf rb,
+void launch_finalize(int kind, int from, const OpDev* ops, const SlotDev* slots, const int* list, int n, RedBuf rb,
                      hipStream_t s) {
   if (n <= 0 || kind == RED_NONE) return;
-  hipLaunchKernelGGL(k_finalize, dim3(n), dim3(64), 0, s, kind, ops, slots, list, rb);
+  hipLaunchKernelGGL(k_finalize, dim3(n), dim3(64), 0, s, kind, from, ops, slots, list, rb);
 }
 
 // ------------------------------------------------------------------------------------

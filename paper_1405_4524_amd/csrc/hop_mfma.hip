@@ -74,7 +74,6 @@ constexpr int SITES_PER_WAVE = BS / WAVES;  // a block covers BS sites, like eve
 constexpr int TROW = 29;                    // uint4 per matrix row (464 B)
 constexpr int TCLO = 24;                    // uint4 column of the clover K step (half 192)
 constexpr int TRW = 5;                      // uint4 per transpose row (80 B)
-constexpr int NTMAX = IL_LANES / 16;        // lane tiles per group
 
 __device__ __forceinline__ uint32_t rot16(uint32_t v) { return (v >> 16) | (v << 16); }
 
@@ -182,57 +181,20 @@ __device__ __forceinline__ void wave_lds_sync() {
 
 }  // namespace
 
-// Data one 16-lane tile (nt) of one site needs, each as the lane's 16 bytes in the B-fragment layout
+// Data one 16-lane tile of one site needs, each as the lane's 16 bytes in the B-fragment layout
 // (chunk gq of its RHS; lanes gq = 3 repeat chunk 0): the six K steps of neighbour data, the
 // clover input (EPI_CLOV) and the other operand of the ALPHA reduction (OMEGA's is the clover
 // input).  One 16-byte load per lane and operand keeps the count of memory instructions, which
 // is what the address units spend their cycles on, low.
 struct TileIn {
-  int nt;
-  uint4 SD;  // this lane's 16 bytes of the site's links (lanes 0..17) and clover (18..35)
+  uint4 SD;  // this lane's 16 bytes of the site's links (lanes 0..17) and clover (18..35); tile 0 only
   uint4 B[6];
   uint4 Bc;
   uint4 Bx;
   int site;
 };
 
-template <int EPI, int RED>
-__device__ __forceinline__ void load_tile(TileIn& d, const char* vin, const char* vaux2, const char* vrh,
-                                          const int (&nbs)[6], const int (&hoff)[6], int site, int NT, int nt,
-                                          int n, int gq) {
-#pragma unroll
-  for (int kt = 0; kt < 6; ++kt) d.B[kt] = gld4(vin + ((long long)nbs[kt] * NT + nt) * 768 + hoff[kt]);
-  const long long own = ((long long)site * NT + nt) * 768 + (gq < 3 ? gq : 0) * 256 + n * 16;
-  if (EPI == 1 || EPI == 3) d.Bc = gld4nt(vaux2 + own);
-  if (RED == RED_ALPHA) d.Bx = gld4nt(vrh + own);
-}
-
-// cb indices of the neighbour site each lane's chunk of K step kt comes from: chunk 4 kt + gq
-// belongs to direction d = (4 kt + gq) / 3, d = 2 mu + f (f = 0 forward, 1 backward)
-__device__ __forceinline__ void site_neighbours(const Geo& g, int site, int po, int gq, int (&nbs)[6]) {
-  int c[4];
-  cb_coords(g, site, po, c);
-  const int xh = c[0] >> 1, x = c[0], y = c[1], z = c[2], t = c[3];
-  const int sy = g.Xh, sz = g.Xh * g.Y, st = g.Xh * g.Y * g.Z;
-  const int row = site - xh;
-  int nb[8];
-  nb[0] = row + ((x + 1 == g.X ? 0 : x + 1) >> 1);
-  nb[1] = row + ((x == 0 ? g.X - 1 : x - 1) >> 1);
-  nb[2] = site + (y == g.Y - 1 ? -(g.Y - 1) * sy : sy);
-  nb[3] = site + (y == 0 ? (g.Y - 1) * sy : -sy);
-  nb[4] = site + (z == g.Z - 1 ? -(g.Z - 1) * sz : sz);
-  nb[5] = site + (z == 0 ? (g.Z - 1) * sz : -sz);
-  nb[6] = site + (t == g.T - 1 ? -(g.T - 1) * st : st);
-  nb[7] = site + (t == 0 ? (g.T - 1) * st : -st);
-  nbs[0] = gq >= 3 ? nb[1] : nb[0];
-  nbs[1] = gq >= 2 ? nb[2] : nb[1];
-  nbs[2] = gq >= 1 ? nb[3] : nb[2];
-  nbs[3] = gq >= 3 ? nb[5] : nb[4];
-  nbs[4] = gq >= 2 ? nb[6] : nb[5];
-  nbs[5] = gq >= 1 ? nb[7] : nb[6];
-}
-
-// A block takes all lane tiles of a group over BS sites (64 per wave) of a 4D brick of the
+// A block takes all NT lane tiles of a group over a 1 / nsub part of BS sites of a 4D brick of the
 // lattice (the whole x row, then y, z, t extents), so that most neighbours of a block's sites
 // are sites of the same block; bricks follow in lexicographic order.  A wave's items are
 // (site, lane tile) pairs, tiles inner: the site's matrix is built once and applied to every
@@ -245,9 +207,11 @@ __device__ __forceinline__ void site_neighbours(const Geo& g, int site, int po, 
 // whole row apart and cost a quarter more L2 misses).  Blocks are not grouped by XCD.  The
 // links, clover and neighbour data of item i + 2 are requested while item i is computed (a ring
 // of three register buffers), and the matrix fragments are read from LDS right before their
-// products.
+// products.  The tile of an item and its buffer are compile-time (the sweep is unrolled over
+// lcm(3, NT) items), so the neighbour addresses are found once per site and a tile is an
+// immediate offset.
 
-template <class P, int EPI, int RED, bool NT3>
+template <class P, int EPI, int RED, int NT>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_hop_mfma(HopMArgs a) {
   using S = typename P::S;
   using M = MM<S>;
@@ -260,7 +224,6 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(3, 3))) void
   const OpDev& op = a.ops[grp.op];
   const Geo g = op.g;
   const int hv = g.hv;
-  const int NT = grp.nt;
   const int po = a.out_par;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -300,9 +263,6 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(3, 3))) void
   const int cdw = 72 + (cblk * 6 + ci) * 6;  // staged dword of the row's six block entries
   // fragment rows (rows 24..31 of the second row tile read valid rows; their outputs are unused)
   const int frow0 = n, frow1 = n + 16 < 24 ? n + 16 : n + 8;
-  int hoff[6];
-#pragma unroll
-  for (int t = 0; t < 6; ++t) hoff[t] = ((4 * t + gq) % 3) * 256 + n * 16;
   const int ochunk = gq < 3 ? gq : 0;  // the chunk this lane loads / stores (gq = 3 repeats 0)
 
   double kp = 1.0;
@@ -318,20 +278,23 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(3, 3))) void
   const char* vaux2 = a.vaux2 >= 0 ? grp.base + (long long)a.vaux2 * vs : nullptr;
   const char* vrh = a.vrhat >= 0 ? grp.base + (long long)a.vrhat * vs : nullptr;
 
-  int myslot[NTMAX];
+  unsigned used = 0;  // bit t: lane n of tile t holds a source
 #pragma unroll
-  for (int t = 0; t < NTMAX; ++t) myslot[t] = (int)gld1(&grp.slot[t * 16 + n]);
-  float red[NTMAX][3];
+  for (int t = 0; t < NT; ++t) used |= ((int)gld1(&grp.slot[t * 16 + n]) >= 0 ? 1u : 0u) << t;
+  float red[NT][3];
 #pragma unroll
-  for (int t = 0; t < NTMAX; ++t) red[t][0] = red[t][1] = red[t][2] = 0.f;
+  for (int t = 0; t < NT; ++t) red[t][0] = red[t][1] = red[t][2] = 0.f;
 
   // zero the matrix once: the padding columns stay zero
   for (int e = lane; e < 24 * TROW; e += 64) (&T[0][0])[e] = make_uint4(0, 0, 0, 0);
   wave_lds_sync();
 
-  const int s0 = tile.y * BS + w * SITES_PER_WAVE;
-  const int cnt = s0 < hv ? (hv - s0 < SITES_PER_WAVE ? hv - s0 : SITES_PER_WAVE) : 0;
-  const int items = cnt * NT;  // items (site, lane tile), tiles inner
+  // the wave's share of the BS sites of the block's brick position: part tile.y % nsub of its
+  // SITES_PER_WAVE sites, so that the waves of a block keep the same (x, y) positions
+  const int nsub = __builtin_amdgcn_readfirstlane(op.nsub);
+  const int spw = SITES_PER_WAVE / nsub;
+  const int s0 = __builtin_amdgcn_readfirstlane(tile.y / nsub * BS + w * SITES_PER_WAVE + tile.y % nsub * spw);
+  const int cnt = s0 < hv ? (hv - s0 < spw ? hv - s0 : spw) : 0;
 
   // a site's links and clover: 36 chunks of 16 bytes, one per lane (lanes 36.. repeat)
   const int sdl = lane < 36 ? lane : lane - 36;
@@ -369,35 +332,52 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     }
   };
 
-  // prefetch cursor: site pk
-  int pk = 0;
-  auto site_at = [&](int p) { return __builtin_amdgcn_readfirstlane(brick_site<true>(g, p)); };
-  // Loads and stores in the sweep are unconditional (positions past the wave's range are clamped
-  // to its last site, whose values are then recomputed and rewritten unchanged), so the number
-  // of memory operations in flight is the same on every path and the waits on them stay exact.
-  // With three tiles per group the ring buffer of an item is its tile (items are (site, tile)
-  // pairs, tiles inner, three buffers), so only buffer 0 takes the site's links and clover:
-  // one load per site instead of one per item.
-  auto prefetch = [&](TileIn& dst, auto with_sd) {
-    const int p = pk < items ? pk : items - 1;
-    const int ntp = __builtin_amdgcn_readfirstlane(p % NT);
-    const int site = site_at(s0 + p / NT);
-    dst.site = site;
-    dst.nt = ntp;
-    if (decltype(with_sd)::value) dst.SD = gld4(sd_base + (size_t)site * 288);
-    int nbs_p[6];
-    site_neighbours(g, site, po, gq, nbs_p);
-    load_tile<EPI, RED>(dst, vin, vaux2, vrh, nbs_p, hoff, site, NT, ntp, n, gq);
-    ++pk;
+  // Prefetch cursor: site ps of the wave's range, its neighbour addresses (found with tile 0, used
+  // by every tile).  Loads are unconditional (past the range the last site is loaded again), so the
+  // number of memory operations in flight is the same on every path and the waits on them stay exact.
+  constexpr long long SITE = NT * 768;  // bytes of a site in a group's vector
+  unsigned hoff[3];                     // chunk (4 kt + gq) % 3 of this lane's RHS, kt = 0..2 (3..5 repeat)
+#pragma unroll
+  for (int t = 0; t < 3; ++t) hoff[t] = ((4 * t + gq) % 3) * 256 + n * 16;
+  const int own = ochunk * 256 + n * 16;
+  SweepCursor cu;
+  int ps = 0, psite = 0;
+  const char* nba[6];
+  auto locate = [&]() {
+    int nb[8];
+    psite = __builtin_amdgcn_readfirstlane(cursor_neighbours(g, cu, po, nb));
+    // chunk 4 kt + gq belongs to direction (4 kt + gq) / 3
+    const int nbs[6] = {gq >= 3 ? nb[1] : nb[0], gq >= 2 ? nb[2] : nb[1], gq >= 1 ? nb[3] : nb[2],
+                        gq >= 3 ? nb[5] : nb[4], gq >= 2 ? nb[6] : nb[5], gq >= 1 ? nb[7] : nb[6]};
+#pragma unroll
+    for (int kt = 0; kt < 6; ++kt) {
+      unsigned h = hoff[kt % 3];
+      asm volatile("" : "+v"(h));  // keeps the 64-bit sums vin + hoff out of registers of their own (they spilled)
+      nba[kt] = vin + ((unsigned long long)(unsigned)nbs[kt] * (unsigned)SITE + h);
+    }
   };
-  // compute cursor: site ck
-  int ck = 0;
-  auto step = [&](TileIn& cur, TileIn& pf, auto may_build, auto pf_sd) {
+  auto prefetch = [&](TileIn& dst, auto tile_c) {
+    constexpr int nt = decltype(tile_c)::value;
+    dst.site = psite;
+    if (nt == 0) dst.SD = gld4(sd_base + (size_t)psite * 288);
+#pragma unroll
+    for (int kt = 0; kt < 6; ++kt) dst.B[kt] = gld4(nba[kt] + nt * 768);
+    const long long at = psite * SITE + nt * 768;
+    if (EPI == 1 || EPI == 3) dst.Bc = gld4nt(vaux2 + at + own);
+    if (RED == RED_ALPHA) dst.Bx = gld4nt(vrh + at + own);
+    if (nt == NT - 1) {  // the site's last tile: on to the next site
+      if (ps + 1 < cnt) {
+        ++ps;
+        cu.next(g);
+      }
+      locate();
+    }
+  };
+  auto step = [&](TileIn& cur, TileIn& pf, auto cur_tile, auto pf_tile) {
+    constexpr int nt = decltype(cur_tile)::value;
     const int site = cur.site;
-    const int nt = cur.nt;
-    const bool live = ck < items;
-    if (decltype(may_build)::value && nt == 0) build(cur.SD);  // this site's matrix, once for all its tiles
-    prefetch(pf, pf_sd);
+    if (nt == 0) build(cur.SD);  // this site's matrix, once for all its tiles
+    prefetch(pf, pf_tile);
     __builtin_amdgcn_sched_barrier(0);  // keep the requests ahead of this item's work
     wave_lds_sync();
     f4v acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
@@ -476,13 +456,10 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(3, 3))) void
       }
       // a select, not a product with 0 or 1: an idle lane's column holds whatever its memory
       // held, and 0 * NaN would reach the partial sums of the same lane in the other tiles
-#pragma unroll
-      for (int t = 0; t < NTMAX; ++t) {
-        const bool keep = live && t == nt && myslot[t] >= 0;
-        red[t][0] += keep ? r0 : 0.f;
-        red[t][1] += keep ? r1 : 0.f;
-        red[t][2] += keep ? r2 : 0.f;
-      }
+      const bool keep = (used >> nt) & 1;
+      red[nt][0] += keep ? r0 : 0.f;
+      red[nt][1] += keep ? r1 : 0.f;
+      red[nt][2] += keep ? r2 : 0.f;
     }
     // to the storage layout through LDS: one 16-byte store per lane (idle lanes write their own
     // unread lane slots; lanes gq = 3 repeat the chunk-0 store of lane gq = 0)
@@ -491,28 +468,37 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     wave_lds_sync();
     const uint4 ob = trb[w][n][ochunk];
     wave_lds_sync();
-    gst4nt(vout + ((long long)site * NT + nt) * 768 + ochunk * 256 + n * 16, ob);
-    ++ck;
+    gst4nt(vout + (site * SITE + nt * 768) + own, ob);
   };
 
-  if (items > 0) {
-    TileIn R0, R1, R2;
-    using yes = std::true_type;
-    using tile0 = std::integral_constant<bool, !NT3>;  // buffers 1 and 2 hold tiles 1 and 2
-    prefetch(R0, yes{});
-    prefetch(R1, tile0{});
-    for (int i = 0; i < items; i += 3) {
-      step(R0, R2, yes{}, tile0{});
-      step(R1, R0, tile0{}, yes{});
-      step(R2, R1, tile0{}, tile0{});
+  if (cnt > 0) {
+    TileIn R[3];
+    cu.init(g, s0);
+    locate();
+    prefetch(R[0], std::integral_constant<int, 0>{});
+    prefetch(R[1], std::integral_constant<int, 1 % NT>{});
+    int left = cnt * NT;  // items
+#define A2A_STEP(i)                                                                                        \
+  step(R[(i) % 3], R[((i) + 2) % 3], std::integral_constant<int, (i) % NT>{}, std::integral_constant<int, ((i) + 2) % NT>{}); \
+  if (--left == 0) break
+    for (;;) {
+      A2A_STEP(0);
+      A2A_STEP(1);
+      A2A_STEP(2);
+      if constexpr (NT == 2) {  // tiles repeat every two items, buffers every three
+        A2A_STEP(3);
+        A2A_STEP(4);
+        A2A_STEP(5);
+      }
     }
+#undef A2A_STEP
   }
 
   if (RED == RED_ALPHA || RED == RED_OMEGA) {
     __syncthreads();  // every wave is done with its matrix: reuse the LDS as scratch
     double* scr = (double*)&tbl[0][0][0];  // [tile][wave][lane][3]
 #pragma unroll
-    for (int t = 0; t < NTMAX; ++t)
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
         double x = (double)red[t][q];
@@ -521,9 +507,9 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(3, 3))) void
         if (lane < 16) scr[((t * WAVES + w) * 16 + lane) * 3 + q] = x;
       }
     __syncthreads();
-    if (threadIdx.x < 48 * NTMAX) {
+    if (threadIdx.x < 48 * NT) {
       const int t = threadIdx.x / 48, m = (threadIdx.x / 3) % 16, q = threadIdx.x % 3;
-      const int sl = t < NT ? grp.slot[t * 16 + m] : -1;
+      const int sl = grp.slot[t * 16 + m];
       if (sl >= 0) {
         double sum = 0.0;
 #pragma unroll
@@ -534,37 +520,46 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(3, 3))) void
   }
 }
 
-template <class P, bool NT3>
+template <class P, int NT>
 static void launch_mfma_nt(const HopMArgs& a, int ntiles, int epi, hipStream_t s) {
   const dim3 g(ntiles), b(BS);
   if (epi == 3) {
     if (a.red == RED_ALPHA)
-      hipLaunchKernelGGL((k_hop_mfma<P, 3, RED_ALPHA, NT3>), g, b, 0, s, a);
+      hipLaunchKernelGGL((k_hop_mfma<P, 3, RED_ALPHA, NT>), g, b, 0, s, a);
     else if (a.red == RED_OMEGA)
-      hipLaunchKernelGGL((k_hop_mfma<P, 3, RED_OMEGA, NT3>), g, b, 0, s, a);
+      hipLaunchKernelGGL((k_hop_mfma<P, 3, RED_OMEGA, NT>), g, b, 0, s, a);
     else
-      hipLaunchKernelGGL((k_hop_mfma<P, 3, RED_NONE, NT3>), g, b, 0, s, a);
+      hipLaunchKernelGGL((k_hop_mfma<P, 3, RED_NONE, NT>), g, b, 0, s, a);
   } else if (epi == 2) {
-    hipLaunchKernelGGL((k_hop_mfma<P, 2, RED_NONE, NT3>), g, b, 0, s, a);
+    hipLaunchKernelGGL((k_hop_mfma<P, 2, RED_NONE, NT>), g, b, 0, s, a);
   } else if (epi == 1) {
     if (a.red == RED_ALPHA)
-      hipLaunchKernelGGL((k_hop_mfma<P, 1, RED_ALPHA, NT3>), g, b, 0, s, a);
+      hipLaunchKernelGGL((k_hop_mfma<P, 1, RED_ALPHA, NT>), g, b, 0, s, a);
     else if (a.red == RED_OMEGA)
-      hipLaunchKernelGGL((k_hop_mfma<P, 1, RED_OMEGA, NT3>), g, b, 0, s, a);
+      hipLaunchKernelGGL((k_hop_mfma<P, 1, RED_OMEGA, NT>), g, b, 0, s, a);
     else
-      hipLaunchKernelGGL((k_hop_mfma<P, 1, RED_NONE, NT3>), g, b, 0, s, a);
+      hipLaunchKernelGGL((k_hop_mfma<P, 1, RED_NONE, NT>), g, b, 0, s, a);
   } else {
-    hipLaunchKernelGGL((k_hop_mfma<P, 0, RED_NONE, NT3>), g, b, 0, s, a);
+    hipLaunchKernelGGL((k_hop_mfma<P, 0, RED_NONE, NT>), g, b, 0, s, a);
   }
 }
 
 template <class P>
 static void launch_mfma_p(const HopMArgs& a, int ntiles, int epi, hipStream_t s) {
-  if (a.nt3)
-    launch_mfma_nt<P, true>(a, ntiles, epi, s);
-  else
-    launch_mfma_nt<P, false>(a, ntiles, epi, s);
+  switch (a.nt) {
+    case 1: launch_mfma_nt<P, 1>(a, ntiles, epi, s); break;
+    case 2: launch_mfma_nt<P, 2>(a, ntiles, epi, s); break;
+    case 3: launch_mfma_nt<P, 3>(a, ntiles, epi, s); break;
+    default: break;
+  }
 }
+
+// A block's four waves sweep BS / nsub sites one after another, about half a microsecond each, so nsub
+// sets how many of the chip's ~768 resident blocks there are and how long the last of them run (Schur
+// pair, 16 sources: 8^3x16, 16 bricks, 199 us whole and 20 us in 16 parts; 16^3x32, 256 bricks, 199 us
+// whole, 107 in two and 113 in four; 28^3x56, 2401 bricks of which no 768 fit evenly, 48 sources, 3827 us
+// whole and 2891 in four; 32^3x64 is the same at one, two and four).
+int il_subblocks(int hv) { return (hv + BS - 1) / BS >= 128 ? 4 : 16; }
 
 bool hop_mfma_supports(int prec, int inv, bool clov, int red, bool aux1) {
   if ((prec != 2 && prec != 3) || aux1) return false;

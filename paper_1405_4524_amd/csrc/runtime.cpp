@@ -51,7 +51,7 @@ int geom_to_geo(const a2a_geom* geom, Geo* g) {
 }
 
 int brick_choices(const Geo& g, int (*out)[3], int maxn) {
-  static const int cand[][3] = {{4, 2, 2}, {2, 2, 4}, {2, 4, 2}, {4, 4, 1}, {8, 2, 1}, {8, 1, 2}, {2, 2, 2},
+  static const int cand[][3] = {{2, 4, 2}, {4, 2, 2}, {2, 2, 4}, {4, 4, 1}, {8, 2, 1}, {8, 1, 2}, {2, 2, 2},
                                 {4, 2, 1}, {2, 2, 1}, {4, 1, 1}, {2, 1, 1}, {1, 1, 1}};
   const int target = std::max(1, BS / std::max(1, (int)g.bxh));
   int n = 0;
@@ -84,6 +84,21 @@ void xcd_order(std::vector<int2>& tiles, bool enable) {
   }
   for (int i = 0; i < n; ++i) out[i] = tiles[start[i % 8] + i / 8];
   tiles.swap(out);
+}
+
+// Matrix-core blocks {group, part} in brick order: each XCD takes runs of up to 16 consecutive bricks
+// with all their nsub parts, so that neighbouring bricks and the parts of one brick share an L2 (Schur
+// pair, 24^3x48 with 32 sources: 1263 us with bricks and parts dealt out one by one, 974 in runs; in
+// XCD slabs 988 there, but 10% slower than runs at 32^3x64, 4510 against 4096 us).
+static void xcd_runs(int group, int nblk, int nsub, std::vector<int2>& out) {
+  const int run = std::max(1, std::min(16, nblk / 8));
+  for (int b0 = 0; b0 < nblk; b0 += 8 * run)
+    for (int j = 0; j < run; ++j)
+      for (int q = 0; q < nsub; ++q)
+        for (int k = 0; k < 8; ++k) {
+          const int b = b0 + k * run + j;
+          if (b < nblk) out.push_back(make_int2(group, b * nsub + q));
+        }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -411,7 +426,9 @@ Solver::Solver(Ctx* c, int p, int r)
     : ctx(c),
       prec(p),
       R(r),
-      R64(c->rhs_block64 == 1 ? 1 : 2),
+      R64(c->rhs_block64),
+      auto_R(r == 0),
+      auto_R64(c->rhs_block64 == 0),
       by(c->brick_by),
       bz(c->brick_bz),
       bt(c->brick_bt),
@@ -491,6 +508,7 @@ int Solver::op_index(int clover_h, double kappa, KappaOp* kop, const GaugeField*
   }
   set_mfma_fields(e.dev, prec, kop, gf);
   e.nblk = (gf->g.hv + BS - 1) / BS;
+  e.dev.nsub = il_subblocks(gf->g.hv);
   ops.push_back(e);
   dirty = true;
   return (int)ops.size() - 1;
@@ -584,24 +602,37 @@ static void vec_lists(const std::vector<Slot*>& live, const std::vector<OpEntry>
     }
     const int e1 = (int)(ils.size() / 16);
     all.reserve(all.size() + (size_t)ops[o].nblk * mine.size());
-    ilt.reserve(ilt.size() + (size_t)ops[o].nblk * (e1 - e0));
-    for (int b = 0; b < ops[o].nblk; ++b) {
+    const int vsub = std::min(ops[o].dev.nsub, VEC_IL_SUB);
+    ilt.reserve(ilt.size() + (size_t)ops[o].nblk * vsub * (e1 - e0));
+    for (int b = 0; b < ops[o].nblk; ++b)
       for (int i : mine) {
         all.push_back(make_int2(i, b));
         if (!live[i]->il_base) nonil.push_back(make_int2(i, b));
       }
+    for (int b = 0; b < ops[o].nblk * vsub; ++b)
       for (int e = e0; e < e1; ++e) ilt.push_back(make_int2(e, b));
-    }
   }
   xcd_order(all, xcd);
   xcd_order(nonil, xcd);
   xcd_order(ilt, xcd);
 }
 
+// RHS per thread of the per-thread stencil.  Two share the links from memory: 2-8% faster for FP64 and
+// FP32 from 24^3x48 on (Schur operator, 16 sources: FP64 2611 against 2647 us, FP32 1305 against 1439).
+// Below that one per thread is (16^3x32: 467 against 494 and 235 against 256 us), since twice the blocks
+// hide more latency; 4^3x8 with 4 sources takes 18 us at one per thread, 30 at two and 50 at four.  With
+// 16-bit storage the registers of a second RHS cost more than its links at every size (32^3x64, 12
+// sources: 1880, 2024 and 2336 us for one, two and four).  Results do not depend on the width.
+static int rhs_width(int prec, long hv) { return prec <= 1 && hv >= (1L << 18) ? 2 : 1; }
+
 int Solver::rebuild() {
   if (!dirty) return A2A_OK;
   ++gen;  // slot indices and tables change: earlier subset uploads are stale
   gc_ops();
+  long hv_max = 0;
+  for (const OpEntry& e : ops) hv_max = std::max(hv_max, (long)e.dev.g.hv);
+  if (auto_R) R = rhs_width(prec, hv_max);
+  if (auto_R64) R64 = rhs_width(0, hv_max);
   // ops and slots
   A2A_TRY(grow(ctx, (void**)&d_ops, &cap_ops, sizeof(OpDev) * std::max<size_t>(1, ops.size())));
   std::vector<OpDev> hops(ops.size());
@@ -616,7 +647,7 @@ int Solver::rebuild() {
     d.op = s->op;
     d.nblk = ops[s->op].nblk;
     d.sid = s->sid;
-    d.pad = 0;
+    d.il = s->il_base ? 1 : 0;
     d.arena[0] = s->lo;
     d.arena[1] = s->hi;
     d.vstride[0] = (long long)s->lo_stride;
@@ -656,10 +687,9 @@ int Solver::rebuild() {
   vec_lists(live, ops, every, ctx->xcd_order, vtiles, nonil, ils, ilt);
   // interleaved groups for the matrix-core stencil, and R-groups of the remaining slots
   std::vector<ILGroupDev> ilg;
-  std::vector<int2> ilh, hnon;
+  std::vector<int2> ilh, ilh_nt[3], hnon;
   std::vector<int> gnon;
   il_mfma = true;
-  il_nt3 = true;
   for (int o = 0; o < (int)ops.size(); ++o) {
     std::map<char*, int> gidx;
     std::vector<int> rest;
@@ -686,7 +716,6 @@ int Solver::rebuild() {
     }
     const int e1 = (int)ilg.size();
     if (e1 > e0 && !(ops[o].dev.HL[0] && ops[o].dev.AF[0] && ops[o].dev.AIF[0])) il_mfma = false;
-    for (int e = e0; e < e1; ++e) il_nt3 = il_nt3 && ilg[e].nt == 3;
     const int g0 = (int)(gnon.size() / R);
     const int ng = (int)((rest.size() + R - 1) / R);
     for (int gi = 0; gi < ng; ++gi)
@@ -694,17 +723,25 @@ int Solver::rebuild() {
         size_t k = (size_t)gi * R + r;
         gnon.push_back(k < rest.size() ? rest[k] : -1);
       }
-    // matrix-core stencil: one block per (group, site block), the group's lane tiles inside
+    // matrix-core stencil: nsub blocks per (group, site block), the group's lane tiles inside; one
+    // launch for the groups of each tile count
     for (int e = e0; e < e1; ++e)
-      for (int b = 0; b < ops[o].nblk; ++b) ilh.push_back(make_int2(e, b));
+      if (mfma_slab)
+        for (int b = 0; b < ops[o].nblk * ops[o].dev.nsub; ++b) ilh_nt[ilg[e].nt - 1].push_back(make_int2(e, b));
+      else
+        xcd_runs(e, ops[o].nblk, ops[o].dev.nsub, ilh_nt[ilg[e].nt - 1]);
     for (int b = 0; b < ops[o].nblk; ++b)
       for (int gi = 0; gi < ng; ++gi) hnon.push_back(make_int2(g0 + gi, b));
   }
   xcd_order(hnon, ctx->xcd_order);
-  // matrix-core blocks: in brick order (XCD k takes every eighth brick), or in XCD slabs (XCD k
-  // takes the k-th eighth of the bricks, so that bricks adjacent in every direction run on the
-  // same XCD at about the same time and share their faces through its L2); a tuned choice
-  xcd_order(ilh, mfma_slab != 0);
+  // matrix-core blocks: in brick order (runs of bricks per XCD), or in XCD slabs (XCD k takes the
+  // k-th eighth of the bricks, so that bricks adjacent in every direction run on the same XCD at
+  // about the same time and share their faces through its L2); a tuned choice
+  for (int k = 0; k < 3; ++k) {
+    xcd_order(ilh_nt[k], mfma_slab != 0);
+    n_il_hop[k] = (int)ilh_nt[k].size();
+    ilh.insert(ilh.end(), ilh_nt[k].begin(), ilh_nt[k].end());
+  }
   A2A_TRY(grow(ctx, (void**)&d_ilgroups, &cap_ilg, sizeof(ILGroupDev) * std::max<size_t>(1, ilg.size())));
   A2A_TRY(grow(ctx, (void**)&d_il_hop_tiles, &cap_ilh, sizeof(int2) * std::max<size_t>(1, ilh.size())));
   A2A_TRY(grow(ctx, (void**)&d_groups_nonil, &cap_gnonil, sizeof(int) * std::max<size_t>(1, gnon.size())));
@@ -713,7 +750,6 @@ int Solver::rebuild() {
   A2A_TRY(upload(ctx, d_il_hop_tiles, ilh.data(), sizeof(int2) * ilh.size()));
   A2A_TRY(upload(ctx, d_groups_nonil, gnon.data(), sizeof(int) * gnon.size()));
   A2A_TRY(upload(ctx, d_hop_nonil, hnon.data(), sizeof(int2) * hnon.size()));
-  n_il_hop_tiles = (int)ilh.size();
   n_hop_nonil = (int)hnon.size();
   A2A_TRY(grow(ctx, (void**)&d_vec_nonil, &cap_nonil, sizeof(int2) * std::max<size_t>(1, nonil.size())));
   A2A_TRY(grow(ctx, (void**)&d_il_slots, &cap_ils, sizeof(int) * std::max<size_t>(1, ils.size())));
@@ -801,8 +837,8 @@ int Solver::upload_subset_vec(const std::vector<int>& idx) {
   return upload_subset(idx, 1);
 }
 
-int Solver::finalize_red(bool sub, int kind) {
-  launch_finalize(kind, d_ops, d_slots, sub ? d_sub_list : nullptr, sub ? sub_n : (int)live.size(), ctx->redbuf(),
+int Solver::finalize_red(bool sub, int kind, int from) {
+  launch_finalize(kind, from, d_ops, d_slots, sub ? d_sub_list : nullptr, sub ? sub_n : (int)live.size(), ctx->redbuf(),
                   ctx->stream);
   A2A_HIP(ctx, hipGetLastError());
   return A2A_OK;
@@ -844,14 +880,15 @@ int Solver::hop(bool sub, int n_tiles, int Rk, int psel, int kprec, int out_par,
   hipEvent_t ev = nullptr;
   if (cls) A2A_TRY(ctx->timing_begin(c, &ev));
   const bool clov = (vaux2 >= 0 && cb != 0.0);
-  if (!sub && psel == 0 && kprec == prec && ctx->mfma && il_mfma && n_il_hop_tiles > 0 &&
-      hop_mfma_supports(kprec, inv, clov, red, vaux1 >= 0)) {
+  const bool on_mfma = !sub && psel == 0 && kprec == prec && ctx->mfma && il_mfma &&
+                       n_il_hop[0] + n_il_hop[1] + n_il_hop[2] > 0 &&
+                       hop_mfma_supports(kprec, inv, clov, red, vaux1 >= 0);
+  if (on_mfma) {
     // interleaved groups on the matrix cores, the other slots with the per-thread stencil
     HopMArgs m{};
     m.ops = d_ops;
     m.slots = d_slots;
     m.groups = d_ilgroups;
-    m.tiles = d_il_hop_tiles;
     m.out_par = out_par;
     m.vin = vin;
     m.vout = vout;
@@ -863,9 +900,14 @@ int Solver::hop(bool sub, int n_tiles, int Rk, int psel, int kprec, int out_par,
     m.gsign = gsign;
     m.gpow = gpow;
     m.red = red;
-    m.nt3 = il_nt3 ? 1 : 0;
     m.rb = ctx->redbuf();
-    launch_hop_mfma(kprec, m, n_il_hop_tiles, inv, clov, ctx->stream);
+    const int2* t = d_il_hop_tiles;
+    for (int k = 0; k < 3; ++k) {
+      m.tiles = t;
+      m.nt = k + 1;
+      launch_hop_mfma(kprec, m, n_il_hop[k], inv, clov, ctx->stream);
+      t += n_il_hop[k];
+    }
     a.groups = d_groups_nonil;
     a.tiles = d_hop_nonil;
     a.brick = n_hop_nonil > blocks;
@@ -890,7 +932,7 @@ int Solver::hop(bool sub, int n_tiles, int Rk, int psel, int kprec, int out_par,
   } else if (cls) {
     A2A_TRY(ctx->timing_end(c, ev, 0.0));
   }
-  if (red != RED_NONE) A2A_TRY(finalize_red(sub, fin >= 0 ? fin : red));
+  if (red != RED_NONE) A2A_TRY(finalize_red(sub, fin >= 0 ? fin : red, on_mfma ? FIN_MFMA : FIN_SLOT));
   return A2A_OK;
 }
 
@@ -911,7 +953,8 @@ int Solver::vec(bool sub, int n_tiles, int kind, int par, int use_inv, int vin, 
   const int tcls = (kind == VK_BICG_XR || kind == VK_CG_XR) ? 2 : (kind == VK_BICG_P || kind == VK_CG_P) ? 3 : 4;
   if (timed) A2A_TRY(ctx->timing_begin(tcls, &ev));
   const int n_il = sub ? sub_ni : n_il_tiles;
-  if (vec_kind_il(kind) && n_il > 0) {  // interleaved slots with the lane mapping, the rest per slot
+  const bool on_il = vec_kind_il(kind) && n_il > 0;
+  if (on_il) {  // interleaved slots with the lane mapping, the rest per slot
     VecArgs b = a;
     b.tiles = sub ? d_sub_tiles + sub_nh + sub_nv + sub_nn : d_il_tiles;
     b.ilslots = sub ? d_sub_il_slots : d_il_slots;
@@ -945,7 +988,7 @@ int Solver::vec(bool sub, int n_tiles, int kind, int par, int use_inv, int vin, 
                   : kind == VK_CG_INIT     ? RED_CG_INIT
                   : kind == VK_CG_RESCALE  ? RED_CG_RU
                                            : RED_NONE;
-  if (red != RED_NONE) A2A_TRY(finalize_red(sub, red));
+  if (red != RED_NONE) A2A_TRY(finalize_red(sub, red, on_il ? FIN_VEC_IL : FIN_SLOT));
   return A2A_OK;
 }
 

@@ -72,6 +72,7 @@ struct OpEntry {
   KappaOp* kop;
   OpDev dev;
   int nblk;
+  int partials() const { return nblk * dev.nsub; }  // most reduction partials of a slot
 };
 
 enum SlotState { SS_NEW = 0, SS_RUN, SS_DONE, SS_FAIL };
@@ -116,12 +117,12 @@ struct TuneCfg {
 struct Solver {
   Ctx* ctx;
   int prec;
-  int R;    // RHS per thread in the stencil
-  int R64;  // RHS per thread in the FP64 stencils of setup, reliable updates and reconstruction
+  int R;    // RHS per thread in the stencil (0 at construction: chosen by rebuild)
+  int R64;  // RHS per thread in the FP64 stencils of setup, reliable updates and reconstruction (likewise)
+  bool auto_R, auto_R64;
   int method = SOLVER_BICGSTAB;  // inner Krylov method of every slot of this solver
   int by = 0, bz = 0, bt = 0;    // brick of the operators this solver creates (0: the lattice's default)
   int mfma_slab = 0;             // matrix-core stencil blocks ordered in XCD slabs
-  bool il_nt3 = false;           // every interleaved group has three lane tiles
   int by64 = 0, bz64 = 0, bt64 = 0;  // brick of the FP64 stencils (reliable updates; 0: the operators')
   size_t peak_live = 0;          // most slots live at once (tail checks)
   int xcd_hop = -1;              // per-thread stencil tiles of full launches in XCD slabs (1/0; -1: the option)
@@ -149,7 +150,7 @@ struct Solver {
          cap_subl = 0, cap_nonil = 0, cap_ils = 0, cap_ilt = 0, cap_subils = 0, cap_ilg = 0, cap_ilh = 0,
          cap_gnonil = 0, cap_hnonil = 0;
   int n_hop_tiles = 0, n_vec_tiles = 0, n_vec_nonil = 0, n_il_tiles = 0;
-  int n_il_hop_tiles = 0, n_hop_nonil = 0;
+  int n_il_hop[3] = {}, n_hop_nonil = 0;  // matrix-core tiles of the groups with 1, 2, 3 lane tiles
   bool il_mfma = false;  // every interleaved group's operator has its matrix-core fields
   // tile and slot counts of the last uploaded subset; its tile buffer holds
   // [hop tiles | per-slot tiles | per-slot tiles of non-interleaved slots | interleaved tiles]
@@ -159,6 +160,10 @@ struct Solver {
 
   Solver(Ctx* c, int p, int r);
   ~Solver();
+  void set_R64(int r) {
+    R64 = r;
+    auto_R64 = false;
+  }
   int op_index(int clover_h, double kappa, KappaOp* kop, const GaugeField* gf);
   int add_slot(Slot* s);
   void gc_ops();
@@ -175,7 +180,7 @@ struct Solver {
   // host buffers of upload_subset's lists, kept between calls
   std::vector<int> sc_groups, sc_ils;
   std::vector<int2> sc_h, sc_v, sc_n, sc_i, sc_all;
-  int finalize_red(bool sub, int kind);
+  int finalize_red(bool sub, int kind, int from = FIN_SLOT);
   // kernel sequences
   int hop(bool sub, int n_tiles, int Rk, int psel, int kprec, int out_par, int vin, int vout, int vaux1, int vaux2,
           int vrhat, double ca, double cb, double gsign, int gpow, int inv, int red, const char* cls,
@@ -227,8 +232,8 @@ struct Ctx {
   std::map<int, std::unique_ptr<CloverField>> clovers;
   unsigned long long use_clock = 0;
   // options
-  int rhs_block = 4;
-  int rhs_block64 = 2;  // RHS per thread of the FP64 stencils (1 or 2)
+  int rhs_block = 0;    // RHS per thread of the per-thread stencil (0: by precision and lattice)
+  int rhs_block64 = 0;  // the same for the FP64 stencils of mixed-precision solves (1 or 2)
   int check_every = 4;
   // reliable-update trigger: the iterated residual has dropped by this factor since the last
   // FP64 residual (FP16 and FP32 storage; BF16's 8-bit mantissa holds about two digits)
