@@ -364,38 +364,57 @@ int dslash_core(Ctx* c, int clover_h, double kappa, int opk, int dagger, int pre
   return rc ? rc : rs;
 }
 
-int contract_ops(Ctx* c, const Geo& g, const double* src, const double* sol, int n, double** O_dev) {
-  const int V3 = g.X * g.Y * g.Z;
-  const long K = 12L * V3;
-  const int ntb = (n + 63) / 64;
-  long want = 4096 / std::max(1, g.T * ntb * ntb);
-  int nchunk = (int)std::max(1L, std::min(want, (K + 255) / 256));
-  void *part = nullptr, *O = nullptr;
-  A2A_TRY(c->dalloc(&part, sizeof(double) * 2 * (size_t)g.T * nchunk * n * n));
-  int rc = c->dalloc(&O, sizeof(double) * 2 * (size_t)g.T * n * n);
-  if (rc) {
-    c->dfree(part);
-    return rc;
+// Results to host memory, after everything queued before: through the context's pinned scalar buffer when
+// they fit (a copy to pageable memory waits for its own staging; the buffer is read before the call returns).
+int copy_to_host(Ctx* c, void* dst, const void* src, size_t n) {
+  if (n <= sizeof(double) * NSCAL * SID_CAP) {
+    A2A_HIP(c, hipMemcpyAsync(c->scal_host, src, n, hipMemcpyDeviceToHost, c->stream));
+    A2A_TRY(c->sync());
+    std::memcpy(dst, c->scal_host, n);
+    return A2A_OK;
   }
-  launch_stoch_ops(g, n, src, sol, (double*)part, nchunk, (double*)O, c->stream);
-  hipError_t e = hipGetLastError();
-  rc = c->sync();
-  c->dfree(part);
-  if (e != hipSuccess) {
-    c->dfree(O);
-    return c->fail(A2A_EDEVICE, std::string("stochastic operators: ") + hipGetErrorString(e));
+  A2A_HIP(c, hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToHost, c->stream));
+  return c->sync();
+}
+
+// Device buffers of one call, given back when it leaves (work of the context's stream that still uses
+// them is ordered before any later use).
+struct Scratch {
+  Ctx* c;
+  std::vector<void*> held;
+  explicit Scratch(Ctx* ctx) : c(ctx) {}
+  ~Scratch() {
+    for (void* p : held) c->dfree(p);
   }
-  if (rc) {
-    c->dfree(O);
-    return rc;
+  int get(double** p, size_t doubles) {
+    void* q = nullptr;
+    A2A_TRY(c->dalloc(&q, sizeof(double) * doubles));
+    held.push_back(q);
+    *p = (double*)q;
+    return A2A_OK;
   }
-  *O_dev = (double*)O;
+};
+
+// eta and X on the device: the caller's device arrays, or copies of its host arrays
+int fields_on_device(Ctx* c, Scratch& mem, bool dev, size_t nel, const double** src, const double** sol) {
+  if (dev) return A2A_OK;
+  for (const double** f : {src, sol}) {
+    double* d;
+    A2A_TRY(mem.get(&d, nel));
+    A2A_HIP(c, hipMemcpyAsync(d, *f, nel * sizeof(double), hipMemcpyHostToDevice, c->stream));
+    *f = d;
+  }
   return A2A_OK;
 }
 
-int copy_to_host(Ctx* c, void* dst, const void* src, size_t n) {
-  A2A_HIP(c, hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToHost, c->stream));
-  return c->sync();
+// O [T][n][n] into O_dev
+int contract_ops(Ctx* c, Scratch& mem, const Geo& g, const double* src, const double* sol, int n, double* O_dev) {
+  const int nchunk = stoch_chunks(g, n, n, g.T);
+  double* part = nullptr;
+  if (nchunk > 1) A2A_TRY(mem.get(&part, 2 * (size_t)g.T * nchunk * n * n));
+  launch_stoch_ops(g, n, src, sol, part, nchunk, O_dev, c->stream);
+  A2A_HIP(c, hipGetLastError());
+  return A2A_OK;
 }
 
 // tiny JSON number lookup: "key": value
@@ -1188,36 +1207,28 @@ static int pion_impl(a2a_ctx* h, const a2a_geom* geom, const double* src, const 
   if (geom_to_geo(geom, &g)) return c->fail(A2A_EINVAL, "bad lattice geometry");
   if (n < 1 || (mode == A2A_PION_UNBIASED && n < 2) || (mode != 0 && mode != 1))
     return c->fail(A2A_EINVAL, "need nrhs >= 2 for the unbiased estimator and mode 0 or 1");
-  const size_t nel = (size_t)n * 24 * 2 * g.hv;
-  const double *ds = src, *dx = sol;
-  void *bs = nullptr, *bx = nullptr;
-  if (!dev) {
-    A2A_TRY(c->dalloc(&bs, nel * sizeof(double)));
-    int rc = c->dalloc(&bx, nel * sizeof(double));
-    if (rc) {
-      c->dfree(bs);
-      return rc;
-    }
-    (void)hipMemcpyAsync(bs, src, nel * sizeof(double), hipMemcpyHostToDevice, c->stream);
-    (void)hipMemcpyAsync(bx, sol, nel * sizeof(double), hipMemcpyHostToDevice, c->stream);
-    ds = (const double*)bs;
-    dx = (const double*)bx;
+  Scratch mem(c);
+  A2A_TRY(fields_on_device(c, mem, dev, (size_t)n * 24 * 2 * g.hv, &src, &sol));
+  // results [corr | O], one copy when O is wanted
+  const size_t nO = 2 * (size_t)g.T * n * n;
+  double *out, *pairs;
+  A2A_TRY(mem.get(&out, 2 * g.T + nO));
+  A2A_TRY(mem.get(&pairs, 2 * pair_corr_partials(g.T, n, 1)));
+  double* O = out + 2 * g.T;
+  A2A_TRY(contract_ops(c, mem, g, src, sol, n, O));
+  launch_pion_corr(g.T, n, O, mode, pairs, out, c->stream);
+  A2A_HIP(c, hipGetLastError());
+  const size_t both = 2 * g.T + nO;
+  if (O_host && sizeof(double) * both <= sizeof(double) * NSCAL * SID_CAP) {
+    A2A_HIP(c, hipMemcpyAsync(c->scal_host, out, sizeof(double) * both, hipMemcpyDeviceToHost, c->stream));
+    A2A_TRY(c->sync());
+    std::memcpy(corr, c->scal_host, sizeof(double) * 2 * g.T);
+    std::memcpy(O_host, c->scal_host + 2 * g.T, sizeof(double) * nO);
+    return A2A_OK;
   }
-  double* O = nullptr;
-  int rc = contract_ops(c, g, ds, dx, n, &O);
-  void* dc = nullptr;
-  if (!rc) rc = c->dalloc(&dc, sizeof(double) * 2 * g.T);
-  if (!rc) {
-    launch_pion_corr(g.T, n, O, mode, (double*)dc, c->stream);
-    rc = copy_to_host(c, corr, dc, sizeof(double) * 2 * g.T);
-  }
-  if (!rc && O_host) rc = copy_to_host(c, O_host, O, sizeof(double) * 2 * (size_t)g.T * n * n);
-  c->sync();
-  c->dfree(dc);
-  c->dfree(O);
-  c->dfree(bs);
-  c->dfree(bx);
-  return rc;
+  A2A_TRY(copy_to_host(c, corr, out, sizeof(double) * 2 * g.T));
+  if (O_host) A2A_TRY(copy_to_host(c, O_host, O, sizeof(double) * nO));
+  return A2A_OK;
 }
 
 extern "C" int a2a_contract_pion_2pt(a2a_ctx* h, const a2a_geom* geom, const double* src, const double* sol, int n,
@@ -1249,15 +1260,12 @@ extern "C" int a2a_contract_pion_2pt_noalloc(a2a_ctx* h, const a2a_geom* geom, c
     return c->fail(A2A_EINVAL, "T nrhs^2 too large for the 32 MiB scratch of the allocation-free contraction (" +
                                    std::to_string((o_bytes + per) >> 20) + " MiB needed at the least)");
   // chunks of the K sum as in the allocating call, as many as the scratch holds
-  const long K = 12L * g.X * g.Y * g.Z;
-  const int ntb = (n + 63) / 64;
-  const long want = 4096 / std::max(1, g.T * ntb * ntb);
   const long fit = (long)((NOALLOC_SCRATCH_BYTES - o_bytes) / per);
-  const int nchunk = (int)std::max(1L, std::min(std::min(want, (K + 255) / 256), fit));
+  const int nchunk = (int)std::max(1L, std::min((long)stoch_chunks(g, n, n, g.T), fit));
   double* O = O_dev ? O_dev : (double*)base;
   double* part = (double*)(base + o_bytes);
   launch_stoch_ops(g, n, src, sol, part, nchunk, O, c->stream);
-  launch_pion_corr(g.T, n, O, mode, corr_dev, c->stream);
+  launch_pion_corr(g.T, n, O, mode, part, corr_dev, c->stream);  // pair partials: at most one [T][n][n] array
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return c->fail(A2A_EDEVICE, std::string("pion contraction: ") + hipGetErrorString(e));
   return c->sync();
@@ -1271,42 +1279,23 @@ static int pipi_impl(a2a_ctx* h, const a2a_geom* geom, const double* src, const 
   Geo g;
   if (geom_to_geo(geom, &g)) return c->fail(A2A_EINVAL, "bad lattice geometry");
   if (n < 4 || n % 4 || n / 4 > 32) return c->fail(A2A_EINVAL, "pi-pi needs nrhs = 4m with 1 <= m <= 32");
-  const size_t nel = (size_t)n * 24 * 2 * g.hv;
-  const double *ds = src, *dx = sol;
-  void *bs = nullptr, *bx = nullptr;
-  if (!dev) {
-    A2A_TRY(c->dalloc(&bs, nel * sizeof(double)));
-    int rc = c->dalloc(&bx, nel * sizeof(double));
-    if (rc) {
-      c->dfree(bs);
-      return rc;
-    }
-    (void)hipMemcpyAsync(bs, src, nel * sizeof(double), hipMemcpyHostToDevice, c->stream);
-    (void)hipMemcpyAsync(bx, sol, nel * sizeof(double), hipMemcpyHostToDevice, c->stream);
-    ds = (const double*)bs;
-    dx = (const double*)bx;
-  }
-  double* O = nullptr;
-  int rc = contract_ops(c, g, ds, dx, n, &O);
-  void *dd = nullptr, *dv = nullptr, *dp = nullptr;
-  if (!rc) rc = c->dalloc(&dd, sizeof(double) * 2 * 4 * g.T);
-  if (!rc) rc = c->dalloc(&dv, sizeof(double) * 2 * g.T);
-  if (!rc && pion) rc = c->dalloc(&dp, sizeof(double) * 2 * g.T);
-  if (!rc) {
-    launch_pipi(g.T, n, O, (double*)dd, (double*)dv, c->stream);
-    if (pion) launch_pion_corr(g.T, n, O, A2A_PION_UNBIASED, (double*)dp, c->stream);
-    rc = copy_to_host(c, diag, dd, sizeof(double) * 2 * 4 * g.T);
-    if (!rc && vac) rc = copy_to_host(c, vac, dv, sizeof(double) * 2 * g.T);
-    if (!rc && pion) rc = copy_to_host(c, pion, dp, sizeof(double) * 2 * g.T);
-  }
-  c->sync();
-  c->dfree(dd);
-  c->dfree(dv);
-  c->dfree(dp);
-  c->dfree(O);
-  c->dfree(bs);
-  c->dfree(bx);
-  return rc;
+  Scratch mem(c);
+  A2A_TRY(fields_on_device(c, mem, dev, (size_t)n * 24 * 2 * g.hv, &src, &sol));
+  double *O, *work, *pairs = nullptr, *out;  // out: diagrams [4][T], loops [T], pion [T]
+  A2A_TRY(mem.get(&O, 2 * (size_t)g.T * n * n));
+  A2A_TRY(mem.get(&work, 2 * pipi_work(g.T, n)));
+  A2A_TRY(mem.get(&out, 2 * 6 * (size_t)g.T));
+  if (pion) A2A_TRY(mem.get(&pairs, 2 * pair_corr_partials(g.T, n, 1)));
+  A2A_TRY(contract_ops(c, mem, g, src, sol, n, O));
+  launch_pipi(g.T, n, O, work, out, out + 8 * g.T, c->stream);
+  if (pion) launch_pion_corr(g.T, n, O, A2A_PION_UNBIASED, pairs, out + 10 * g.T, c->stream);
+  A2A_HIP(c, hipGetLastError());
+  std::vector<double> hres((pion ? 12 : 10) * (size_t)g.T);
+  A2A_TRY(copy_to_host(c, hres.data(), out, sizeof(double) * hres.size()));
+  std::memcpy(diag, hres.data(), sizeof(double) * 8 * g.T);
+  if (vac) std::memcpy(vac, hres.data() + 8 * g.T, sizeof(double) * 2 * g.T);
+  if (pion) std::memcpy(pion, hres.data() + 10 * g.T, sizeof(double) * 2 * g.T);
+  return A2A_OK;
 }
 
 extern "C" int a2a_contract_pipi_2pt(a2a_ctx* h, const a2a_geom* geom, const double* src, const double* sol, int n,
@@ -1451,13 +1440,7 @@ extern "C" int a2a_contract_gram_2pt_dev(a2a_ctx* h, const a2a_geom* geom, const
   Geo g;
   A2A_TRY(fill_geo(c, geom, nrhs, t_src, &g));
   const int n = nrhs;
-  const long K = 12L * g.X * g.Y * g.Z;
-  const int ntb = (n + 63) / 64;
-  auto chunks = [&](int nt) {
-    long want = 4096 / std::max(1, nt * ntb * ntb);
-    return (int)std::max(1L, std::min(want, (K + 255) / 256));
-  };
-  const int ce = chunks(1), cf = chunks(g.T);
+  const int ce = stoch_chunks(g, n, n, 1), cf = stoch_chunks(g, n, n, g.T);
   const size_t nn = (size_t)n * n;
   void *part = nullptr, *E = nullptr, *F = nullptr, *dc = nullptr;
   A2A_TRY(c->dalloc(&part, sizeof(double) * 2 * std::max((size_t)ce, (size_t)g.T * cf) * nn));
@@ -1510,7 +1493,6 @@ extern "C" int a2a_contract_pipi_mixed_dev(a2a_ctx* h, const a2a_geom* geom, con
   if (n1 < 1 || n2 < 1) return c->fail(A2A_EINVAL, "n1 and n2 must be positive");
   if (t0 < 0 || t0 >= g.T) return c->fail(A2A_EINVAL, "source timeslice out of range");
   const int T = g.T;
-  const long K = 12L * g.X * g.Y * g.Z;
   // the timeslice Gram matrices <a_r, b_s>_t (no gamma_5): rows from `a`, columns from `b`
   struct Gram {
     const double* a;
@@ -1526,8 +1508,7 @@ extern "C" int a2a_contract_pipi_mixed_dev(a2a_ctx* h, const a2a_geom* geom, con
                 {sol2, n2, point_sol, 12, 0, T, 0, 0}};       // B[t][j][k] = <X2_j, Sp_k>_t
   size_t part_elems = 0;
   for (Gram& q : gm) {
-    const long tiles = (long)q.nt * ((q.na + 63) / 64) * ((q.nb + 63) / 64);
-    q.nchunk = (int)std::max(1L, std::min(4096 / std::max(1L, tiles), (K + 255) / 256));
+    q.nchunk = stoch_chunks(g, q.na, q.nb, q.nt);
     q.elems = (size_t)q.nt * q.na * q.nb;
     part_elems = std::max(part_elems, q.elems * q.nchunk);
   }
@@ -1583,21 +1564,15 @@ extern "C" int a2a_dilute_dev(a2a_ctx* h, const a2a_geom* geom, const double* no
   return c->sync();
 }
 
-// exp(-i p.y) on the spatial sites of a timeslice (x fastest), the angle reduced exactly
-static void momentum_phase(const Geo& g, const int* p, std::vector<double>& ph) {
-  const long V3 = (long)g.X * g.Y * g.Z;
-  ph.resize(2 * V3);
-  const double two_pi = 6.283185307179586476925;
-  long s = 0;
-  for (int z = 0; z < g.Z; ++z)
-    for (int y = 0; y < g.Y; ++y)
-      for (int x = 0; x < g.X; ++x, ++s) {
-        const long ax = (((long)p[0] * x) % g.X + g.X) % g.X, ay = (((long)p[1] * y) % g.Y + g.Y) % g.Y,
-                   az = (((long)p[2] * z) % g.Z + g.Z) % g.Z;
-        const double f = (double)ax / g.X + (double)ay / g.Y + (double)az / g.Z;
-        ph[2 * s] = std::cos(two_pi * f);
-        ph[2 * s + 1] = -std::sin(two_pi * f);
-      }
+// the phases of momentum p and of -p in the batch (p reduced to the lattice; each distinct one once)
+static int batch_phase(const Geo& g, const int* p, int sign, MomBatch* mb) {
+  const long long L[3] = {g.X, g.Y, g.Z};
+  long long q[3];
+  for (int k = 0; k < 3; ++k) q[k] = ((sign * (long long)p[k]) % L[k] + L[k]) % L[k];
+  for (int i = 0; i < mb->nph; ++i)
+    if (std::equal(q, q + 3, mb->p[i])) return i;
+  std::copy(q, q + 3, mb->p[mb->nph]);
+  return mb->nph++;
 }
 
 extern "C" int a2a_contract_pion_mom_dev(a2a_ctx* h, const a2a_geom* geom, const double* src, const double* sol,
@@ -1626,57 +1601,63 @@ extern "C" int a2a_contract_pion_mom_dev(a2a_ctx* h, const a2a_geom* geom, const
       for (int i = 0; i < nv; ++i)
         for (int q = 0; q < per_t; ++q) rows[(size_t)t * na + i * per_t + q] = i * group + per_t * t + q;
   }
-  const long K = 12L * g.X * g.Y * g.Z;
-  const int ntb = (n + 63) / 64, nta = (na + 63) / 64;
-  long want = 4096 / std::max(1, g.T * ntb * nta);
-  const int nchunk = (int)std::max(1L, std::min(want, (K + 255) / 256));
-  const size_t nn = (size_t)na * n;
-  const size_t V3 = (size_t)g.X * g.Y * g.Z;
-  void *part = nullptr, *Op = nullptr, *Om = nullptr, *ph = nullptr, *dc = nullptr, *drows = nullptr;
-  A2A_TRY(c->dalloc(&part, sizeof(double) * 2 * (size_t)g.T * nchunk * nn));
-  int rc = c->dalloc(&Op, sizeof(double) * 2 * (size_t)g.T * nn);
-  if (!rc) rc = c->dalloc(&Om, sizeof(double) * 2 * (size_t)g.T * nn);
-  if (!rc) rc = c->dalloc(&ph, sizeof(double) * 4 * V3);
-  if (!rc) rc = c->dalloc(&dc, sizeof(double) * 2 * g.T);
-  if (!rc && by_time) {
-    rc = c->dalloc(&drows, sizeof(int) * rows.size());
-    if (!rc && hipMemcpyAsync(drows, rows.data(), sizeof(int) * rows.size(), hipMemcpyHostToDevice, c->stream) !=
-                   hipSuccess)
-      rc = c->fail(A2A_EDEVICE, "row table upload failed");
+  const size_t nn = (size_t)na * n, V3 = (size_t)g.X * g.Y * g.Z;
+  const bool by_sc = scheme == A2A_DILUTE_SC || scheme == A2A_DILUTE_TSC;
+  // momenta in batches whose operators (and their chunk sums) stay below MOM_BATCH_BYTES, at least one
+  constexpr double MOM_BATCH_BYTES = 1e9;
+  Scratch rowmem(c);
+  int* drows = nullptr;
+  if (by_time) {
+    double* p = nullptr;
+    A2A_TRY(rowmem.get(&p, (rows.size() + 1) / 2));
+    drows = (int*)p;
+    A2A_HIP(c, hipMemcpyAsync(drows, rows.data(), sizeof(int) * rows.size(), hipMemcpyHostToDevice, c->stream));
   }
-  std::vector<double> hp, hm;
-  for (int m = 0; m < nmom && !rc; ++m) {
-    const int* p = moms + 3 * m;
-    const int q[3] = {-p[0], -p[1], -p[2]};
-    momentum_phase(g, p, hp);
-    momentum_phase(g, q, hm);
-    double* php = (double*)ph;
-    double* phm = php + 2 * V3;
-    if (hipMemcpyAsync(php, hp.data(), sizeof(double) * 2 * V3, hipMemcpyHostToDevice, c->stream) != hipSuccess ||
-        hipMemcpyAsync(phm, hm.data(), sizeof(double) * 2 * V3, hipMemcpyHostToDevice, c->stream) != hipSuccess) {
-      rc = c->fail(A2A_EDEVICE, "phase upload failed");
-      break;
+  int most = MOM_BATCH;
+  for (int m0 = 0; m0 < nmom;) {
+    MomBatch mb{};
+    MomPairs mp{};
+    int nchunk = 1;
+    for (; mp.nm < most && m0 + mp.nm < nmom; ++mp.nm) {
+      MomBatch more = mb;
+      const int ip = batch_phase(g, moms + 3 * (m0 + mp.nm), 1, &more);
+      const int im = batch_phase(g, moms + 3 * (m0 + mp.nm), -1, &more);
+      const int ch = by_sc ? stoch_sc_chunks(g, nv, more.nph, n) : stoch_chunks(g, more.nph * na, n, g.T);
+      if (mp.nm > 0 && 16.0 * g.T * more.nph * (double)nn * (ch > 1 ? ch + 1 : 1) > MOM_BATCH_BYTES) break;
+      mb = more;
+      nchunk = ch;
+      mp.ip[mp.nm] = ip;
+      mp.im[mp.nm] = im;
     }
-    const int* dr = (const int*)drows;
-    launch_stoch_ops(g, n, src, sol, (double*)part, nchunk, (double*)Op, c->stream, 1, 0, g.T, php, dr, na);
-    launch_stoch_ops(g, n, src, sol, (double*)part, nchunk, (double*)Om, c->stream, 1, 0, g.T, phm, dr, na);
-    if (by_time)
-      launch_pion_mom_rows(g.T, n, na, dr, group, mode, (const double*)Op, (const double*)Om, (double*)dc,
-                           c->stream);
+    Scratch mem(c);
+    const size_t nO = 2 * (size_t)g.T * mb.nph * nn;
+    double *O, *part = nullptr, *ph, *pairs, *dc;
+    int rc = mem.get(&O, nO);
+    if (!rc && nchunk > 1) rc = mem.get(&part, nO * nchunk);
+    if (!rc) rc = mem.get(&ph, 2 * V3 * mb.nph);
+    if (!rc) rc = mem.get(&pairs, 2 * (by_time ? (size_t)mp.nm * g.T * g.T : pair_corr_partials(g.T, n, mp.nm)));
+    if (!rc) rc = mem.get(&dc, 2 * (size_t)mp.nm * g.T);
+    if (rc == A2A_ENOMEM && mp.nm > 1) {  // a batch that does not fit: one momentum at a time
+      c->err.clear();
+      most = 1;
+      continue;
+    }
+    if (rc) return rc;
+    launch_phases(g, mb, ph, c->stream);
+    if (by_sc)
+      launch_stoch_sc(g, n, nv, mb.nph, group, by_time, src, sol, ph, part, nchunk, O, c->stream);
     else
-      launch_pion_mom(g.T, n, group, mode, (const double*)Op, (const double*)Om, (double*)dc, c->stream);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) rc = c->fail(A2A_EDEVICE, std::string("momentum contraction: ") + hipGetErrorString(e));
-    if (!rc) rc = copy_to_host(c, corr + 2 * (size_t)m * g.T, dc, sizeof(double) * 2 * g.T);
+      launch_stoch_ops(g, n, src, sol, part, nchunk, O, c->stream, 1, 0, g.T, ph, drows, mb.nph * na, na);
+    if (by_time)
+      launch_pion_mom_rows(g.T, n, na, mb.nph, drows, group, mode, mp, O, pairs, dc, c->stream);
+    else
+      launch_pion_mom(g.T, n, mb.nph, group, mode, mp, O, pairs, dc, c->stream);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return c->fail(A2A_EDEVICE, std::string("momentum contraction: ") + hipGetErrorString(e));
+    A2A_TRY(copy_to_host(c, corr + 2 * (size_t)m0 * g.T, dc, sizeof(double) * 2 * mp.nm * g.T));
+    m0 += mp.nm;
   }
-  c->sync();
-  c->dfree(part);
-  c->dfree(Op);
-  c->dfree(Om);
-  c->dfree(ph);
-  c->dfree(dc);
-  c->dfree(drows);
-  return rc;
+  return A2A_OK;
 }
 
 // =========================================================================================

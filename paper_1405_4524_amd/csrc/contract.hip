@@ -5,157 +5,253 @@
 //
 // is, per timeslice, a complex matrix product E_t^dag (gamma_5 X_t) with inner dimension
 // K = 12 L^3 taken straight from the canonical [src][t][z][y][x][spin][colour] arrays, where
-// each (source, timeslice) column is contiguous.  Blocks own a K-chunk of one timeslice and
-// a 64x64 tile of (a, b); operand tiles are staged through LDS (coalesced along K) and the
-// products run on the FP64 matrix cores, each wave a 16 x 64 strip of the tile.  Chunk partials
-// are summed in fixed order.
+// each (source, timeslice) column is contiguous.
 #include "a2a_contract.h"
 #include "a2a_kernels.h"
 
 namespace a2a {
 
-constexpr int CT = 64;   // output tile edge
-constexpr int KC = 16;   // complex elements per K step
-
-// rows (optional, [T][na]): row r of timeslice t is source rows[t na + r] (sources supported on
-// that timeslice only, e.g. after time dilution); without it na = n and row r is source r.
 typedef double d4v __attribute__((ext_vector_type(4)));
 
-// NC: 16-column tiles per wave (1..4, from n); columns past n are staged as zeros
-template <int NC>
-__global__ __launch_bounds__(256) void k_stoch_partial(int n, int na, long V, int V3, int nchunk, int kchunk,
-                                                        int g5, int t_first, const double* __restrict__ eta,
-                                                        const double* __restrict__ X,
-                                                        const double* __restrict__ phase,
-                                                        const int* __restrict__ rows, double* partial) {
-  __shared__ double2 Es[CT][KC + 1];
-  __shared__ double2 Xs[CT][KC + 1];
-  // grid: x = output tile (row tile x column tile), y = timeslice, z = K chunk (<= 4096)
-  const int chunk = blockIdx.z, tl = blockIdx.y, t = t_first + tl;
-  const int ntb = (n + CT - 1) / CT;
-  const int ta = blockIdx.x / ntb, tb = blockIdx.x % ntb;
-  const int a0 = ta * CT, b0 = tb * CT;
-  const long K = 12L * V3;
-  const long k_begin = (long)chunk * kchunk;
-  const long k_end = min(K, k_begin + kchunk);
-  // wave w owns output rows a0 + 16 w .. + 15 and NC 16-column tiles of the block; a wave whose
-  // rows are all past na issues no products (wave-uniform)
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int li = lane & 15, lk = lane >> 4;
-  const bool row_on = a0 + 16 * w < na;
-  d4v cr[NC], ci[NC];
+// One wave computes a tile of 16 NA x 16 NB entries over a chunk of sites on the FP64 matrix cores,
+// its operands loaded from memory in fragment layout: v_mfma_f64_16x16x4 takes A[l % 16][l / 16] from
+// lane l, and with the K step's four elements taken as component c of the four spins of one site, lane
+// (row, spin) reads its row's 48 contiguous bytes of that spin and gamma_5 is a sign per lane.  Every
+// element is read once per tile, no LDS and no barrier are used, and the next sites' operands load
+// during the products of the current ones (9 tiles of a 48-source block: 108 products a site, ~7000
+// cycles).  Rows and columns past na and n read the last one; their entries are not stored.  Chunk
+// partials are summed in fixed order.
+//   The largest tile that n allows (up to 4 x 4) reads the operands the fewest times.  Memory bounds it up
+// to 48 sources: rows are a power of two apart, and what counts is how long a row is read before the next
+// one (sites per iteration: one 9.3 ms, two 8.05 ms for 32^3x64 with 48 sources, where 64 x 64 block tiles
+// staged through LDS between barriers took 13.3 ms, 33 TFLOP/s and 2.9 TB/s; now 58 TFLOP/s and
+// 4.8 TB/s); from 64 sources on the FP64 matrix rate does (57 TFLOP/s at 128 and 256).
+// Virtual rows: row r < na is source r % ns (or rows[t ns + r % ns]) times phase r / ns of the phases
+// [na / ns][V3], so that all momenta of a call share one pass over X.
+struct StochArgs {
+  int n, na, ns;         // columns, virtual rows, rows per phase
+  int nchunk, spc;       // chunks of a timeslice, sites per chunk
+  int nta, ntb;          // row and column tiles
+  int nt, t_first, g5;
+  long V;
+  int V3;
+  const double* eta;
+  const double* X;
+  const double* phase;
+  const int* rows;
+  double* partial;
+};
+
+// sites per iteration: as many as the registers of one wave per SIMD hold twice (they divide X Y Z)
+constexpr int stoch_sites(int na, int nb) {
+  return 16 * na * nb + 96 * (na + nb) <= 450 ? 4 : 16 * na * nb + 48 * (na + nb) <= 450 ? 2 : 1;
+}
+
+template <int NA, int NB>
+__global__ __launch_bounds__(64) void k_stoch_partial(StochArgs a) {
+  constexpr int SN = stoch_sites(NA, NB);
+  // blocks: the tiles of one (timeslice, chunk) share its rows through the L2 of one XCD
+  const int ntile = a.nta * a.ntb, units = a.nt * a.nchunk;
+  const int g = blockIdx.x / (8 * ntile), r = blockIdx.x % (8 * ntile);
+  const int unit = g * 8 + r % 8, tile = r / 8;
+  if (unit >= units) return;
+  const int tl = unit % a.nt, chunk = unit / a.nt, t = a.t_first + tl;
+  const int a0 = tile / a.ntb * 16 * NA, b0 = tile % a.ntb * 16 * NB;
+  const int lane = threadIdx.x, li = lane & 15, q = lane >> 4;
+  const int s0 = chunk * a.spc, s1 = min(a.V3, s0 + a.spc);
+  const double sg = a.g5 && q >= 2 ? -1.0 : 1.0;  // gamma_5 = diag(1,1,-1,-1)
+  const double *pe[NA], *px[NB], *pf[NA];
 #pragma unroll
-  for (int c = 0; c < NC; ++c) cr[c] = ci[c] = d4v{0.0, 0.0, 0.0, 0.0};
-  const size_t src_stride = (size_t)12 * V;  // complex per source
-  const size_t tbase = (size_t)t * V3 * 12;
-  // operand loads of the stage at k0 (64 rows x 16 complex of each operand, 4 per thread):
-  // every load is unconditional, from a clamped in-range element, and out-of-range elements
-  // are zeroed afterwards.  (Loading the next stage during the products cost occupancy and
-  // gained nothing.)
-  double2 pe[4], px[4];
-  auto load = [&](long k0) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int e = threadIdx.x + q * 256;
-      const int row = e / KC, kk = e % KC;
-      const long k = k0 + kk;
-      const long kc = min(k, k_end - 1);
-      const int ra = min(a0 + row, na - 1), rb = min(b0 + row, n - 1);
-      const int ar = rows ? rows[(size_t)t * na + ra] : ra;
-      double2 ev = *(const double2*)(eta + 2 * ((size_t)ar * src_stride + tbase + kc));
-      double2 xv = *(const double2*)(X + 2 * ((size_t)rb * src_stride + tbase + kc));
-      if (phase) {  // eta conj(f) with f = exp(-i p.y): the product below takes conj(eta) f
-        const double fr = phase[2 * (kc / 12)], fi = phase[2 * (kc / 12) + 1];
-        ev = make_double2(ev.x * fr + ev.y * fi, ev.y * fr - ev.x * fi);
-      }
-      const double sg = (g5 && (kc % 12) >= 6) ? -1.0 : 1.0;  // gamma_5 = diag(1,1,-1,-1)
-      const bool kin = k < k_end;
-      pe[q] = kin && a0 + row < na ? ev : make_double2(0.0, 0.0);
-      px[q] = kin && b0 + row < n ? make_double2(sg * xv.x, sg * xv.y) : make_double2(0.0, 0.0);
-    }
-  };
-  for (long k0 = k_begin; k0 < k_end; k0 += KC) {
-    load(k0);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int e = threadIdx.x + q * 256;
-      Es[e / KC][e % KC] = pe[q];
-      Xs[e / KC][e % KC] = px[q];
-    }
-    __syncthreads();
-    if (row_on) {
-      // v_mfma_f64_16x16x4: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16]; four real
-      // products per complex K step: Re += er xr + ei xi, Im += er xi - ei xr, issued tile-
-      // interleaved so that consecutive products accumulate into different registers
-#pragma unroll
-      for (int ks = 0; ks < KC / 4; ++ks) {
-        const double2 e = Es[16 * w + li][4 * ks + lk];
-        double2 x[NC];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) x[c] = Xs[16 * c + li][4 * ks + lk];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) cr[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(e.x, x[c].x, cr[c], 0, 0, 0);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) ci[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(e.x, x[c].y, ci[c], 0, 0, 0);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) cr[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(e.y, x[c].y, cr[c], 0, 0, 0);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) ci[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(-e.y, x[c].x, ci[c], 0, 0, 0);
-      }
-    }
-    __syncthreads();
+  for (int i = 0; i < NA; ++i) {
+    const int ra = min(a0 + 16 * i + li, a.na - 1), ph = ra / a.ns, rr = ra - ph * a.ns;
+    const int ar = a.rows ? a.rows[(size_t)t * a.ns + rr] : rr;
+    pe[i] = a.eta + 2 * ((size_t)ar * 12 * a.V + (size_t)t * 12 * a.V3 + 3 * q);
+    pf[i] = a.phase ? a.phase + 2 * (size_t)ph * a.V3 : nullptr;
   }
-  // element q of a 16 x 16 accumulator tile is row 4 q + lane / 16, column lane % 16
-  double* out = partial + (((size_t)tl * nchunk + chunk) * na) * n * 2;
-  if (row_on)
 #pragma unroll
-    for (int c = 0; c < NC; ++c)
+  for (int j = 0; j < NB; ++j) {
+    const int rb = min(b0 + 16 * j + li, a.n - 1);
+    px[j] = a.X + 2 * ((size_t)rb * 12 * a.V + (size_t)t * 12 * a.V3 + 3 * q);
+  }
+  d4v cr[NA][NB], ci[NA][NB];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int a = a0 + 16 * w + 4 * q + lk, b = b0 + 16 * c + li;
-        if (a < na && b < n) {
-          out[2 * ((size_t)a * n + b)] = cr[c][q];
-          out[2 * ((size_t)a * n + b) + 1] = ci[c][q];
+  for (int i = 0; i < NA; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) cr[i][j] = ci[i][j] = d4v{0.0, 0.0, 0.0, 0.0};
+  double2 ne[NA][SN][3], nx[NB][SN][3], nf[NA][SN];
+  auto load = [&](int s) {
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+      for (int u = 0; u < SN; ++u) {
+        const double2* p = (const double2*)(pe[i] + (size_t)24 * (s + u));
+#pragma unroll
+        for (int c = 0; c < 3; ++c) ne[i][u][c] = p[c];
+        if (a.phase) nf[i][u] = *(const double2*)(pf[i] + (size_t)2 * (s + u));
+      }
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int u = 0; u < SN; ++u) {
+        const double2* p = (const double2*)(px[j] + (size_t)24 * (s + u));
+#pragma unroll
+        for (int c = 0; c < 3; ++c) nx[j][u][c] = p[c];
+      }
+  };
+  if (s0 < s1) load(s0);
+  for (int s = s0; s < s1; s += SN) {
+    double2 e[NA][SN][3], x[NB][SN][3];
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+      for (int u = 0; u < SN; ++u)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          e[i][u][c] = ne[i][u][c];
+          if (a.phase)  // eta conj(f) with f = exp(-i p.y): the product below takes conj(eta) f
+            e[i][u][c] = make_double2(ne[i][u][c].x * nf[i][u].x + ne[i][u][c].y * nf[i][u].y,
+                                      ne[i][u][c].y * nf[i][u].x - ne[i][u][c].x * nf[i][u].y);
         }
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int u = 0; u < SN; ++u)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) x[j][u][c] = make_double2(sg * nx[j][u][c].x, sg * nx[j][u][c].y);
+    load(min(s + SN, s1 - SN));
+    // four real products per complex K step: Re += er xr + ei xi, Im += er xi - ei xr, tile-interleaved
+    // so that consecutive products accumulate into different registers
+#pragma unroll
+    for (int u = 0; u < SN; ++u)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j)
+            cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(e[i][u][c].x, x[j][u][c].x, cr[i][j], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j)
+            ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(e[i][u][c].x, x[j][u][c].y, ci[i][j], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j)
+            cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(e[i][u][c].y, x[j][u][c].y, cr[i][j], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j)
+            ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(-e[i][u][c].y, x[j][u][c].x, ci[i][j], 0, 0, 0);
+      }
+  }
+  // element k of a 16 x 16 accumulator tile is row 4 k + lane / 16, column lane % 16
+  double* out = a.partial + ((size_t)tl * a.nchunk + chunk) * a.na * a.n * 2;
+#pragma unroll
+  for (int i = 0; i < NA; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int ra = a0 + 16 * i + 4 * k + q, rb = b0 + 16 * j + li;
+        if (ra < a.na && rb < a.n)
+          *(double2*)(out + 2 * ((size_t)ra * a.n + rb)) = make_double2(cr[i][j][k], ci[i][j][k]);
       }
 }
 
-__global__ void k_stoch_sum(int n, int na, int T, int nchunk, const double* partial, double* O) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;  // over T*na*n complex
-  const long per = (long)na * n;
-  if (i >= (long)T * per) return;
-  const long t = i / per, ab = i % per;
-  double sr = 0.0, si = 0.0;
-  for (int c = 0; c < nchunk; ++c) {
-    const double* p = partial + (((size_t)t * nchunk + c) * per + ab) * 2;
-    sr += p[0];
-    si += p[1];
+// chunk sums; blockDim.y splits the chunks, in a fixed order
+__global__ __launch_bounds__(256) void k_stoch_sum(long per, int T, int nchunk, const double* partial, double* O) {
+  __shared__ double2 part[256];
+  const int nx = blockDim.x, ny = blockDim.y;
+  const long i = (long)blockIdx.x * nx + threadIdx.x;  // over T * per complex
+  double2 s = make_double2(0.0, 0.0);
+  if (i < (long)T * per) {
+    const long t = i / per, ab = i % per;
+    for (int c = threadIdx.y; c < nchunk; c += ny) {
+      const double2 p = ((const double2*)partial)[((size_t)t * nchunk + c) * per + ab];
+      s.x += p.x;
+      s.y += p.y;
+    }
   }
-  O[2 * i] = sr;
-  O[2 * i + 1] = si;
+  if (ny > 1) {
+    part[threadIdx.y * nx + threadIdx.x] = s;
+    __syncthreads();
+    if (threadIdx.y) return;
+    for (int y = 1; y < ny; ++y) {
+      s.x += part[y * nx + threadIdx.x].x;
+      s.y += part[y * nx + threadIdx.x].y;
+    }
+  }
+  if (i < (long)T * per) ((double2*)O)[i] = s;
+}
+
+// tiles of 16 a wave takes along a dimension of n entries: the blocks of at most four tiles that waste least
+static int stoch_tiles(int n) {
+  const int tiles = (n + 15) / 16, blocks = (tiles + 3) / 4;
+  return (tiles + blocks - 1) / blocks;
+}
+
+// Chunks of a timeslice: one wave per SIMD (more of them read from more places at once and were slower,
+// 32^3x64 with 32 sources 6.1 ms at one and 7.2 ms at two per SIMD); twice as many where a wave reads few
+// distinct rows.
+int stoch_chunks(const Geo& g, int na, int n, int nt) {
+  const int V3 = g.X * g.Y * g.Z, ta = stoch_tiles(na), tb = stoch_tiles(n);
+  const long waves = std::min(na, n) <= 8 ? 2048 : 1024;
+  const long tiles = (long)nt * ((na + 16 * ta - 1) / (16 * ta)) * ((n + 16 * tb - 1) / (16 * tb));
+  return (int)std::max(1L, std::min(waves / std::max(1L, tiles), (long)V3 / stoch_sites(ta, tb)));
+}
+
+template <int NA>
+static void launch_stoch_na(int nb, const StochArgs& a, dim3 grid, hipStream_t s) {
+  switch (nb) {
+    case 1: hipLaunchKernelGGL((k_stoch_partial<NA, 1>), grid, dim3(64), 0, s, a); break;
+    case 2: hipLaunchKernelGGL((k_stoch_partial<NA, 2>), grid, dim3(64), 0, s, a); break;
+    case 3: hipLaunchKernelGGL((k_stoch_partial<NA, 3>), grid, dim3(64), 0, s, a); break;
+    default: hipLaunchKernelGGL((k_stoch_partial<NA, 4>), grid, dim3(64), 0, s, a); break;
+  }
+}
+
+static void launch_stoch_sum(long per, int nt, int nchunk, const double* partial, double* O, hipStream_t s) {
+  const long tot = (long)nt * per;
+  // few outputs: split the chunks of an output over threads too
+  const int ny = tot >= 65536 || nchunk < 16 ? 1 : 16, nx = 256 / ny;
+  hipLaunchKernelGGL(k_stoch_sum, dim3((unsigned)((tot + nx - 1) / nx)), dim3(nx, ny), 0, s, per, nt, nchunk, partial, O);
 }
 
 void launch_stoch_ops(const Geo& g, int n, const double* eta, const double* X, double* partial, int nchunk,
                       double* O, hipStream_t s, int g5, int t_first, int nt, const double* phase, const int* rows,
-                      int na) {
-  const int V3 = g.X * g.Y * g.Z;
-  const long V = (long)V3 * g.T;
-  const long K = 12L * V3;
+                      int na, int ns) {
+  StochArgs a{};
+  a.V3 = g.X * g.Y * g.Z;
+  a.V = (long)a.V3 * g.T;
   if (nt < 0) nt = g.T;
-  long kchunk = (K + nchunk - 1) / nchunk;
-  kchunk = ((kchunk + KC - 1) / KC) * KC;
   if (na <= 0) na = n;  // rows == null: eta rows 0 .. na - 1
-  const int ntb = (n + CT - 1) / CT, nta = (na + CT - 1) / CT;
-  dim3 grid((unsigned)(nta * ntb), nt, nchunk);
-  // column tiles per wave: enough for n (a single column block), else all four
-  const int nc = ntb > 1 ? 4 : (n + 15) / 16;
-  auto kern = nc == 1 ? k_stoch_partial<1> : nc == 2 ? k_stoch_partial<2> : nc == 3 ? k_stoch_partial<3>
-                                                                                       : k_stoch_partial<4>;
-  hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, n, na, V, V3, nchunk, (int)kchunk, g5, t_first, eta, X, phase, rows,
-                     partial);
-  const long tot = (long)nt * na * n;
-  hipLaunchKernelGGL(k_stoch_sum, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, n, na, nt, nchunk, partial,
-                     O);
+  a.n = n;
+  a.na = na;
+  a.ns = ns > 0 ? ns : na;
+  a.nchunk = nchunk;
+  const int ta = stoch_tiles(na), tb = stoch_tiles(n), sn = stoch_sites(ta, tb);
+  a.spc = ((a.V3 + nchunk - 1) / nchunk + sn - 1) / sn * sn;
+  a.nt = nt;
+  a.t_first = t_first;
+  a.g5 = g5;
+  a.eta = eta;
+  a.X = X;
+  a.phase = phase;
+  a.rows = rows;
+  a.partial = nchunk > 1 ? partial : O;  // a single chunk needs no sum
+  a.nta = (na + 16 * ta - 1) / (16 * ta);
+  a.ntb = (n + 16 * tb - 1) / (16 * tb);
+  const dim3 grid((unsigned)(((long)nt * nchunk + 7) / 8 * 8 * a.nta * a.ntb));
+  switch (ta) {
+    case 1: launch_stoch_na<1>(tb, a, grid, s); break;
+    case 2: launch_stoch_na<2>(tb, a, grid, s); break;
+    case 3: launch_stoch_na<3>(tb, a, grid, s); break;
+    default: launch_stoch_na<4>(tb, a, grid, s); break;
+  }
+  if (nchunk > 1) launch_stoch_sum((long)na * n, nt, nchunk, partial, O, s);
 }
 
 // Gram form of sum_{z,x} tr[S1 S2^dag]: corr[t] = (1/n^2) sum_ij E[i][j] F[t][j][i] with
@@ -283,96 +379,313 @@ void launch_pipi_mixed(int T, int t0, int n1, int n2, const double* Pn, const do
                      1.0 / ((double)n1 * (double)n2), Pn, partial, diag, pieces);
 }
 
-// Momentum-projected pion from O(t, p) and O(t, -p): corr[dt] = sum_t0 sum_{a, b}
-// Op[t0 + dt][a][b] Om[t0][b][a] over pairs of sources from different noise vectors (a / group
-// != b / group), normalised by 1 / (T n (n - 1)) with n = N / group noise vectors (mode 0), or
-// over all pairs without normalisation (mode 3).
-__global__ __launch_bounds__(256) void k_pion_mom(int T, int N, int group, int mode, const double* Op,
-                                                  const double* Om, double* corr) {
-  const int dt = blockIdx.x;
-  const long per = (long)N * N;
+// ------------------------------------------------------------------------------------
+// momentum phases and spin-colour diluted operators
+// ------------------------------------------------------------------------------------
+// f[k][y] = exp(-i p_k.y) on the spatial sites of a timeslice (x fastest), the angle reduced exactly
+__global__ __launch_bounds__(256) void k_phases(int X, int Y, int V3, MomBatch m, double* f) {
+  const int s = blockIdx.x * 256 + threadIdx.x, k = blockIdx.y;
+  if (s >= V3) return;
+  const int x = s % X, y = s / X % Y, z = s / (X * Y), Z = V3 / (X * Y);
+  const long long* p = m.p[k];
+  const double g = (double)(p[0] * x % X) / X + (double)(p[1] * y % Y) / Y + (double)(p[2] * z % Z) / Z;
+  double sn, cs;
+  sincospi(2.0 * g, &sn, &cs);
+  ((double2*)f)[(size_t)k * V3 + s] = make_double2(cs, -sn);
+}
+
+void launch_phases(const Geo& g, const MomBatch& m, double* f, hipStream_t s) {
+  const int V3 = g.X * g.Y * g.Z;
+  hipLaunchKernelGGL(k_phases, dim3((unsigned)((V3 + 255) / 256), (unsigned)m.nph), dim3(256), 0, s, g.X, g.Y, V3, m, f);
+}
+
+// Stochastic operators of spin-colour diluted sources (schemes SC and TSC): the source (i, c) is zero
+// but for component c, so row (ph, i, c) of O(t) sums over the sites only, with column elements
+// X_b(y)_c: a twelfth of the dense products, and of the X rows only one read for all momenta.  One
+// wave per component (12 per block), 16 NA virtual rows (phase, noise vector) x 32 columns; the block
+// stages 4 sites of its columns in LDS (768-byte runs), every wave takes its component from
+// there as the K step's four sites.  8^3x16, 768 sources, 11 phases: the dense products over zeros took
+// 13.9 ms, this 0.72 (40 TFLOP/s of matrix products; 384 blocks of one per CU are one and a half rounds,
+// and more, shorter ones cost as much in repeated rows or partial sums).
+constexpr int SC_SITES = 4;                 // sites per stage (one K step)
+constexpr int SC_COLS = 2;                  // column tiles of a block
+constexpr int SC_ROW = SC_SITES * 12 + 1;   // complex per staged column (padded: 16 columns, distinct banks)
+
+struct ScArgs {
+  int n, nv, nph, group, time;  // columns, noise vectors, phases, pieces per noise vector, time-diluted
+  int nchunk, spc, V3;          // chunks of a timeslice, sites per chunk (a multiple of SC_SITES)
+  long V;
+  const double* eta;
+  const double* X;
+  const double* phase;
+  double* partial;
+};
+
+template <int NA>
+__global__ __launch_bounds__(768) void k_stoch_sc(ScArgs a) {
+  constexpr int NB = SC_COLS;
+  __shared__ double2 xs[2][16 * NB * SC_ROW];
+  const int c = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 15, q = lane >> 4;
+  const int b0 = blockIdx.x * 16 * NB, t = blockIdx.y;
+  const int chunk = blockIdx.z % a.nchunk, v0 = blockIdx.z / a.nchunk * 16 * NA, vr = a.nph * a.nv;
+  const int s0 = chunk * a.spc, s1 = min(a.V3, s0 + a.spc);
+  const double sg = c >= 6 ? -1.0 : 1.0;  // gamma_5
+  const double *pe[NA], *pf[NA];
+#pragma unroll
+  for (int i = 0; i < NA; ++i) {
+    const int v = min(v0 + 16 * i + li, vr - 1), ph = v / a.nv, nz = v - ph * a.nv;
+    const size_t src = (size_t)nz * a.group + (a.time ? 12 * t : 0) + c;
+    pe[i] = a.eta + 2 * (src * 12 * a.V + (size_t)t * 12 * a.V3 + c);
+    pf[i] = a.phase + 2 * (size_t)ph * a.V3;
+  }
+  // staging: 48 lanes load the 768 bytes of four sites of one column; a thread takes two columns
+  const int sr = threadIdx.x / 48, sc = threadIdx.x % 48;
+  const double2* px = (const double2*)a.X + (size_t)t * 12 * a.V3;
+  const double2* px0 = px + (size_t)min(b0 + sr, a.n - 1) * 12 * a.V;
+  const double2* px1 = px + (size_t)min(b0 + sr + 16, a.n - 1) * 12 * a.V;
+  double2 st0, st1;
+  auto fetch = [&](int s) {  // past the timeslice: its last element
+    const int e = min(12 * s + sc, 12 * a.V3 - 1);
+    st0 = px0[e];
+    st1 = px1[e];
+  };
+  auto put = [&](int buf) {
+    xs[buf][sr * SC_ROW + sc] = st0;
+    xs[buf][(sr + 16) * SC_ROW + sc] = st1;
+  };
+  double2 ne[NA], nf[NA];
+  auto load = [&](int s) {
+    const int y = min(s + q, a.V3 - 1);
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+      ne[i] = *(const double2*)(pe[i] + (size_t)24 * y);
+      nf[i] = *(const double2*)(pf[i] + (size_t)2 * y);
+    }
+  };
+  d4v cr[NA][NB], ci[NA][NB];
+#pragma unroll
+  for (int i = 0; i < NA; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) cr[i][j] = ci[i][j] = d4v{0.0, 0.0, 0.0, 0.0};
+  fetch(s0);
+  load(s0);
+  put(0);
+  __syncthreads();
+  for (int s = s0, buf = 0; s < s1; s += SC_SITES, buf ^= 1) {
+    double2 e[NA], x[NB];
+    const bool in = s + q < s1;  // sites past the chunk count nothing
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {  // eta conj(f) g5, as in the dense kernel
+      e[i].x = in ? sg * (ne[i].x * nf[i].x + ne[i].y * nf[i].y) : 0.0;
+      e[i].y = in ? sg * (ne[i].y * nf[i].x - ne[i].x * nf[i].y) : 0.0;
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      x[j] = xs[buf][(16 * j + li) * SC_ROW + 12 * q + c];
+      if (!in) x[j] = make_double2(0.0, 0.0);
+    }
+    fetch(s + SC_SITES);
+    load(s + SC_SITES);
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(e[i].x, x[j].x, cr[i][j], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(e[i].x, x[j].y, ci[i][j], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(e[i].y, x[j].y, cr[i][j], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(-e[i].y, x[j].x, ci[i][j], 0, 0, 0);
+    put(buf ^ 1);
+    __syncthreads();
+  }
+  const int na = 12 * a.nv;
+  double2* out = (double2*)a.partial + ((size_t)t * a.nchunk + chunk) * a.nph * na * a.n;
+#pragma unroll
+  for (int i = 0; i < NA; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int v = v0 + 16 * i + 4 * k + q, b = b0 + 16 * j + li;
+        if (v < vr && b < a.n) {
+          const int ph = v / a.nv, nz = v - ph * a.nv;
+          out[((size_t)ph * na + 12 * nz + c) * a.n + b] = make_double2(cr[i][j][k], ci[i][j][k]);
+        }
+      }
+}
+
+static int sc_tiles(int vr) { return std::min(3, (vr + 15) / 16); }
+// chunks of a timeslice: a block per CU, at least four stages each
+int stoch_sc_chunks(const Geo& g, int nv, int nph, int n) {
+  const int V3 = g.X * g.Y * g.Z, vr = nv * nph, ra = 16 * sc_tiles(vr);
+  const long blocks = (long)((n + 16 * SC_COLS - 1) / (16 * SC_COLS)) * g.T * ((vr + ra - 1) / ra);
+  return (int)std::max(1L, std::min(256 / std::max(1L, blocks), (long)V3 / (4 * SC_SITES)));
+}
+
+void launch_stoch_sc(const Geo& g, int n, int nv, int nph, int group, int time, const double* eta, const double* X,
+                     const double* phase, double* partial, int nchunk, double* O, hipStream_t s) {
+  ScArgs a{};
+  a.n = n;
+  a.nv = nv;
+  a.nph = nph;
+  a.group = group;
+  a.time = time;
+  a.V3 = g.X * g.Y * g.Z;
+  a.V = (long)a.V3 * g.T;
+  a.nchunk = nchunk;
+  a.spc = ((a.V3 + nchunk - 1) / nchunk + SC_SITES - 1) / SC_SITES * SC_SITES;
+  a.eta = eta;
+  a.X = X;
+  a.phase = phase;
+  a.partial = nchunk > 1 ? partial : O;
+  const int vr = nv * nph, na = sc_tiles(vr);
+  const dim3 grid((unsigned)((n + 16 * SC_COLS - 1) / (16 * SC_COLS)), (unsigned)g.T,
+                  (unsigned)(nchunk * ((vr + 16 * na - 1) / (16 * na)))), blk(768);
+  if (na == 1) hipLaunchKernelGGL(k_stoch_sc<1>, grid, blk, 0, s, a);
+  if (na == 2) hipLaunchKernelGGL(k_stoch_sc<2>, grid, blk, 0, s, a);
+  if (na == 3) hipLaunchKernelGGL(k_stoch_sc<3>, grid, blk, 0, s, a);
+  if (nchunk > 1) launch_stoch_sum((long)nph * 12 * nv * n, g.T, nchunk, partial, O, s);
+}
+
+// ------------------------------------------------------------------------------------
+// pair correlators: corr[m][dt] = sum_t0 sum_ab keep_ab O[t0 + dt][ip_m][a][b] O[t0][im_m][b][a]
+// with O [T][nph][n][n]; keep drops pairs of one noise vector (a / group == b / group) when skip is set
+// (group 1: the diagonal).
+// ------------------------------------------------------------------------------------
+// For one (a, b) the sum is a circular correlation over time, so a block takes an EB x EB patch of
+// (a, b) and all timeslices: O is read once per dt tile, and the T^2 products per entry come from LDS
+// (one block per dt reading every O(t) took 285 us for T = 64 and 48 sources, this 17).
+// A thread owns one of DT separations and a part of the t0 tile; block partials are summed in block order.
+template <int DT, int EB>
+__global__ __launch_bounds__(256) void k_pair_corr(int T, int n, int nph, int group, int skip, MomPairs mp,
+                                                   const double* O, double* partial) {
+  constexpr int E = EB * EB, PARTS = 256 / DT, PER = DT / PARTS;  // PER t0 per part and tile of DT
+  __shared__ double2 xs[2 * DT - 1][E + 1], ys[DT][E + 1];
+  const int nb = (n + EB - 1) / EB;
+  const int a0 = blockIdx.x / nb * EB, b0 = blockIdx.x % nb * EB, d0 = blockIdx.y * DT, m = blockIdx.z;
+  const int ip = mp.ip[m], im = mp.im[m];
+  const double2* Oc = (const double2*)O;
+  const int dt = threadIdx.x % DT, part = threadIdx.x / DT;
+  double vr = 0.0, vi = 0.0;
+  for (int t0 = 0; t0 < T; t0 += DT) {
+    for (int k = threadIdx.x; k < (2 * DT - 1) * E; k += 256) {  // rows t0 + d0 + 0 .. 2 DT - 2 (mod T)
+      const int r = k / E, e = k % E, a = a0 + e / EB, b = b0 + e % EB;
+      const bool on = a < n && b < n && !(skip && a / group == b / group);
+      const int t1 = (t0 + d0 + r) % T;
+      xs[r][e] = on ? Oc[(((size_t)t1 * nph + ip) * n + a) * n + b] : make_double2(0.0, 0.0);
+    }
+    for (int k = threadIdx.x; k < DT * E; k += 256) {
+      const int r = k / E, e = k % E, b = b0 + e / EB, a = a0 + e % EB;  // consecutive a: O[b][a] in runs
+      ys[r][(e % EB) * EB + e / EB] =
+          t0 + r < T && a < n && b < n ? Oc[(((size_t)(t0 + r) * nph + im) * n + b) * n + a] : make_double2(0.0, 0.0);
+    }
+    __syncthreads();
+    for (int k = 0; k < PER; ++k) {
+      const int r = part * PER + k;
+#pragma unroll 8
+      for (int e = 0; e < E; ++e) {
+        const double2 x = xs[r + dt][e], y = ys[r][e];
+        vr += x.x * y.x - x.y * y.y;
+        vi += x.x * y.y + x.y * y.x;
+      }
+    }
+    __syncthreads();
+  }
+  double2* red = &xs[0][0];  // [PARTS][DT]
+  red[part * DT + dt] = make_double2(vr, vi);
+  __syncthreads();
+  if (part == 0 && d0 + dt < T) {
+    for (int k = 1; k < PARTS; ++k) {
+      vr += red[k * DT + dt].x;
+      vi += red[k * DT + dt].y;
+    }
+    ((double2*)partial)[((size_t)m * T + d0 + dt) * gridDim.x + blockIdx.x] = make_double2(vr, vi);
+  }
+}
+
+// corr[i] = sum of its nblk partials, in a fixed order, divided by norm
+__global__ __launch_bounds__(256) void k_corr_sum(int nblk, double norm, const double* partial, double* corr) {
+  const double2* p = (const double2*)partial + (size_t)blockIdx.x * nblk;
   double v[2] = {0.0, 0.0};
-  for (long e = threadIdx.x; e < (long)T * per; e += 256) {
-    const int t0 = (int)(e / per);
-    const int a = (int)((e % per) / N), b = (int)(e % N);
-    if (mode == 0 && a / group == b / group) continue;
-    const int t1 = (t0 + dt) % T;
-    const double* x = Op + 2 * ((size_t)t1 * per + (size_t)a * N + b);
-    const double* y = Om + 2 * ((size_t)t0 * per + (size_t)b * N + a);
-    v[0] += x[0] * y[0] - x[1] * y[1];
-    v[1] += x[0] * y[1] + x[1] * y[0];
+  for (int k = threadIdx.x; k < nblk; k += 256) {
+    v[0] += p[k].x;
+    v[1] += p[k].y;
   }
   block_sum_n<2, 256>(v);
-  const double nv = (double)(N / group);
-  const double norm = mode == 0 ? 1.0 / ((double)T * nv * (nv - 1.0)) : 1.0;
-  if (threadIdx.x < 2) corr[2 * dt + threadIdx.x] = (threadIdx.x == 0 ? v[0] : v[1]) * norm;
+  if (threadIdx.x < 2) corr[2 * blockIdx.x + threadIdx.x] = (threadIdx.x == 0 ? v[0] : v[1]) / norm;
 }
 
-void launch_pion_mom(int T, int N, int group, int mode, const double* Op, const double* Om, double* corr,
-                     hipStream_t s) {
-  hipLaunchKernelGGL(k_pion_mom, dim3((unsigned)T), dim3(256), 0, s, T, N, group, mode, Op, Om, corr);
-}
-
-// The same for time-diluted sources, from the compact operators Op[t][r][b] of the na sources
-// rows[t][r] supported on timeslice t: a source a contributes to O(t) only at its own timeslice.
-__global__ __launch_bounds__(256) void k_pion_mom_rows(int T, int N, int na, const int* rows, int group, int mode,
-                                                       const double* Op, const double* Om, double* corr) {
-  const int dt = blockIdx.x;
-  const long per = (long)na * na;
+// time-diluted sources: O [T][nph][na][n] holds the na sources rows[t][r] supported on timeslice t; a
+// source contributes to O(t) only at its own timeslice.  One block per (t0, dt, m).
+__global__ __launch_bounds__(256) void k_pair_corr_rows(int T, int N, int na, int nph, const int* rows, int group,
+                                                        int skip, MomPairs mp, const double* O, double* partial) {
+  const int t0 = blockIdx.x, dt = blockIdx.y, m = blockIdx.z, t1 = (t0 + dt) % T;
+  const double2* Op = (const double2*)O + ((size_t)t1 * nph + mp.ip[m]) * na * N;
+  const double2* Om = (const double2*)O + ((size_t)t0 * nph + mp.im[m]) * na * N;
   double v[2] = {0.0, 0.0};
-  for (long e = threadIdx.x; e < (long)T * per; e += 256) {
-    const int t0 = (int)(e / per);
-    const int r1 = (int)((e % per) / na), r0 = (int)(e % na);
-    const int t1 = (t0 + dt) % T;
+  for (long e = threadIdx.x; e < (long)na * na; e += 256) {
+    const int r1 = (int)(e / na), r0 = (int)(e % na);
     const int a = rows[(size_t)t1 * na + r1], b = rows[(size_t)t0 * na + r0];
-    if (mode == 0 && a / group == b / group) continue;
-    const double* x = Op + 2 * (((size_t)t1 * na + r1) * N + b);
-    const double* y = Om + 2 * (((size_t)t0 * na + r0) * N + a);
-    v[0] += x[0] * y[0] - x[1] * y[1];
-    v[1] += x[0] * y[1] + x[1] * y[0];
+    if (skip && a / group == b / group) continue;
+    const double2 x = Op[(size_t)r1 * N + b], y = Om[(size_t)r0 * N + a];
+    v[0] += x.x * y.x - x.y * y.y;
+    v[1] += x.x * y.y + x.y * y.x;
   }
   block_sum_n<2, 256>(v);
+  if (threadIdx.x < 2)
+    partial[2 * (((size_t)m * T + dt) * T + t0) + threadIdx.x] = threadIdx.x == 0 ? v[0] : v[1];
+}
+
+// few timeslices: 16 separations x 16 parts on 8 x 8 patches; else 64 x 4 on 4 x 4
+static int pair_edge(int T) { return T <= 16 ? 8 : 4; }
+size_t pair_corr_partials(int T, int n, int nm) {
+  const size_t nb = (n + pair_edge(T) - 1) / pair_edge(T);
+  return (size_t)nm * T * nb * nb;
+}
+
+static void launch_pair_corr(int T, int n, int nph, int group, int skip, const MomPairs& mp, double norm, const double* O,
+                             double* partial, double* corr, hipStream_t s) {
+  const int eb = pair_edge(T), nb = (n + eb - 1) / eb;
+  if (T <= 16)
+    hipLaunchKernelGGL((k_pair_corr<16, 8>), dim3((unsigned)(nb * nb), 1, mp.nm), dim3(256), 0, s, T, n, nph, group, skip,
+                       mp, O, partial);
+  else
+    hipLaunchKernelGGL((k_pair_corr<64, 4>), dim3((unsigned)(nb * nb), (unsigned)((T + 63) / 64), mp.nm), dim3(256), 0, s, T,
+                       n, nph, group, skip, mp, O, partial);
+  hipLaunchKernelGGL(k_corr_sum, dim3((unsigned)(mp.nm * T)), dim3(256), 0, s, nb * nb, norm, partial, corr);
+}
+
+// Momentum-projected pions over pairs of sources from different noise vectors, normalised by
+// 1 / (T n (n - 1)) with n = N / group noise vectors (mode 0), or over all pairs without normalisation
+// (mode 3).
+void launch_pion_mom(int T, int N, int nph, int group, int mode, const MomPairs& mp, const double* O, double* partial,
+                     double* corr, hipStream_t s) {
   const double nv = (double)(N / group);
-  const double norm = mode == 0 ? 1.0 / ((double)T * nv * (nv - 1.0)) : 1.0;
-  if (threadIdx.x < 2) corr[2 * dt + threadIdx.x] = (threadIdx.x == 0 ? v[0] : v[1]) * norm;
+  launch_pair_corr(T, N, nph, group, mode == 0, mp, mode == 0 ? (double)T * nv * (nv - 1.0) : 1.0, O, partial, corr, s);
 }
 
-void launch_pion_mom_rows(int T, int N, int na, const int* rows, int group, int mode, const double* Op,
-                          const double* Om, double* corr, hipStream_t s) {
-  hipLaunchKernelGGL(k_pion_mom_rows, dim3((unsigned)T), dim3(256), 0, s, T, N, na, rows, group, mode, Op, Om, corr);
+void launch_pion_mom_rows(int T, int N, int na, int nph, const int* rows, int group, int mode, const MomPairs& mp,
+                          const double* O, double* partial, double* corr, hipStream_t s) {
+  hipLaunchKernelGGL(k_pair_corr_rows, dim3((unsigned)T, (unsigned)T, mp.nm), dim3(256), 0, s, T, N, na, nph, rows, group,
+                     mode == 0, mp, O, partial);
+  const double nv = (double)(N / group);
+  hipLaunchKernelGGL(k_corr_sum, dim3((unsigned)(mp.nm * T)), dim3(256), 0, s, T,
+                     mode == 0 ? (double)T * nv * (nv - 1.0) : 1.0, partial, corr);
 }
 
-// ------------------------------------------------------------------------------------
 // pion correlator from O.  mode 0: unbiased a != b, 1/(T N (N-1)); 1: all pairs 1/(T N^2)
-// (the form printed with eq. stoop); 2, 3: the same two sums without normalisation.
-// ------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_pion(int T, int n, const double* O, int mode, double* corr) {
-  const int dt = blockIdx.x;
-  double sr = 0.0, si = 0.0;
-  const long per = (long)n * n;
-  for (long e = threadIdx.x; e < (long)T * per; e += 256) {
-    const int t0 = (int)(e / per);
-    const int a = (int)((e % per) / n), b = (int)(e % n);
-    if ((mode == 0 || mode == 2) && a == b) continue;
-    const int t1 = (t0 + dt) % T;
-    const double* x = O + 2 * ((size_t)t1 * per + (size_t)a * n + b);
-    const double* y = O + 2 * ((size_t)t0 * per + (size_t)b * n + a);
-    sr += x[0] * y[0] - x[1] * y[1];
-    si += x[0] * y[1] + x[1] * y[0];
-  }
-  double v[2] = {sr, si};
-  block_sum_all<2, 256>(v);
-  if (threadIdx.x == 0) {
-    double norm = 1.0;
-    if (mode == 0) norm = (double)T * n * (n - 1);
-    if (mode == 1) norm = (double)T * n * n;
-    corr[2 * dt] = v[0] / norm;
-    corr[2 * dt + 1] = v[1] / norm;
-  }
-}
-
-void launch_pion_corr(int T, int n, const double* O, int mode, double* corr, hipStream_t s) {
-  hipLaunchKernelGGL(k_pion, dim3(T), dim3(256), 0, s, T, n, O, mode, corr);
+// (the form printed with eq. stoop).  partial: pair_corr_partials(T, n, 1) complex
+void launch_pion_corr(int T, int n, const double* O, int mode, double* partial, double* corr, hipStream_t s) {
+  MomPairs mp{};
+  mp.nm = 1;
+  launch_pair_corr(T, n, 1, 1, mode == 0, mp, (double)T * n * (mode == 0 ? n - 1 : n), O, partial, corr, s);
 }
 
 // ------------------------------------------------------------------------------------
@@ -385,107 +698,109 @@ void launch_pion_corr(int T, int n, const double* O, int mode, double* corr, hip
 //   D2(dt) = 1/T sum_t0 tr[B^{12}(t0) B^{23}(t1) B^{34}(t1) B^{41}(t0)] / m^4
 //   D3(dt) = 1/T sum_t0 tr[B^{12}(t1) B^{23}(t1) B^{34}(t0) B^{41}(t0)] / m^4
 //   vac(t) = L^{12}(t,t)
-// One block per dt; the 4-fold traces use two m x m products staged in LDS (m <= 32).
+// By cyclicity the 4-fold traces are tr[P(t0) Q(t1)] and tr[R(t1) S(t0)] with P = B^{41} B^{12},
+// Q = B^{23} B^{34}, R = B^{12} B^{23}, S = B^{34} B^{41}, so the matrix products are made once per
+// timeslice (4 T of them, not 4 T^2) and every (t0, t1) needs four sums over m^2 entries.  One block per
+// dt that formed the products for each t0 in turn took 620 us for T = 64 and 48 sources, these two 35.
 // ------------------------------------------------------------------------------------
 constexpr int PIPI_MMAX = 32;
 
-__device__ __forceinline__ cx<double> oblk(const double* O, int N, int m, int t, int g, int h, int i, int j) {
-  const double* p = O + 2 * (((size_t)t * N + g * m + i) * N + h * m + j);
-  return mk(p[0], p[1]);
-}
-
-__device__ cx<double> loop2_block(const double* O, int N, int m, int g, int h, int t1, int t2, double* lds) {
-  double sr = 0.0, si = 0.0;
+// w [6][T][m][m]: P, R and, transposed, Q, S, B^{21}, B^{43}; loops [2][T]: tr[B^{12} B^{21}], tr[B^{34} B^{43}]
+__global__ __launch_bounds__(256) void k_pipi_products(int T, int N, const double* O, double* w, double* loops) {
+  __shared__ double2 A[PIPI_MMAX * PIPI_MMAX], B[PIPI_MMAX * (PIPI_MMAX + 1)];
+  const int t = blockIdx.x, k = blockIdx.y, m = N / 4;
+  const double2* Ot = (const double2*)O + (size_t)t * N * N;
+  // groups of the factors (rows, columns): P, R, Q, S, then the two loops
+  const int gr[6] = {3, 0, 1, 2, 0, 2}, gm[6] = {0, 1, 2, 3, 1, 3}, gc[6] = {1, 2, 3, 0, 0, 2};
   for (int e = threadIdx.x; e < m * m; e += 256) {
     const int i = e / m, j = e % m;
-    cx<double> p = oblk(O, N, m, t1, g, h, i, j) * oblk(O, N, m, t2, h, g, j, i);
-    sr += p.re;
-    si += p.im;
-  }
-  double v[2] = {sr, si};
-  block_sum_all<2, 256>(v);
-  __shared__ cx<double> res;
-  if (threadIdx.x == 0) res = mk(v[0], v[1]);
-  __syncthreads();
-  cx<double> r = res;
-  __syncthreads();
-  return r;
-}
-
-__device__ cx<double> loop4_block(const double* O, int N, int m, int ta, int tb, int tc, int td, cx<double>* M1,
-                                  cx<double>* M2, double* lds) {
-  for (int e = threadIdx.x; e < m * m; e += 256) {  // M1 = B12(ta) B23(tb)
-    const int i = e / m, k = e % m;
-    cx<double> acc = mk(0.0, 0.0);
-    for (int j = 0; j < m; ++j) acc = acc + oblk(O, N, m, ta, 0, 1, i, j) * oblk(O, N, m, tb, 1, 2, j, k);
-    M1[e] = acc;
+    A[e] = Ot[(size_t)(gr[k] * m + i) * N + gm[k] * m + j];
+    B[i * (m + 1) + j] = Ot[(size_t)(gm[k] * m + i) * N + gc[k] * m + j];
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < m * m; e += 256) {  // M2 = M1 B34(tc)
-    const int i = e / m, l = e % m;
-    cx<double> acc = mk(0.0, 0.0);
-    for (int k = 0; k < m; ++k) acc = acc + M1[i * m + k] * oblk(O, N, m, tc, 2, 3, k, l);
-    M2[e] = acc;
-  }
-  __syncthreads();
-  double sr = 0.0, si = 0.0;
-  for (int e = threadIdx.x; e < m * m; e += 256) {  // tr(M2 B41(td))
-    const int i = e / m, l = e % m;
-    cx<double> p = M2[i * m + l] * oblk(O, N, m, td, 3, 0, l, i);
-    sr += p.re;
-    si += p.im;
-  }
-  double v[2] = {sr, si};
-  block_sum_all<2, 256>(v);
-  __shared__ cx<double> res;
-  if (threadIdx.x == 0) res = mk(v[0], v[1]);
-  __syncthreads();
-  cx<double> r = res;
-  __syncthreads();
-  return r;
-}
-
-__global__ __launch_bounds__(256) void k_pipi(int T, int N, const double* O, double* diag, double* vac) {
-  __shared__ cx<double> M1[PIPI_MMAX * PIPI_MMAX];
-  __shared__ cx<double> M2[PIPI_MMAX * PIPI_MMAX];
-  __shared__ double lds[8];
-  const int dt = blockIdx.x;
-  const int m = N / 4;
-  const double m2 = (double)m * m, m4 = m2 * m2;
-  cx<double> d0 = mk(0.0, 0.0), d1 = d0, d2 = d0, d3 = d0;
-  for (int t0 = 0; t0 < T; ++t0) {
-    const int t1 = (t0 + dt) % T;
-    cx<double> l12 = loop2_block(O, N, m, 0, 1, t1, t0, lds);
-    cx<double> l34 = loop2_block(O, N, m, 2, 3, t1, t0, lds);
-    d0 = d0 + (1.0 / (m2 * m2)) * (l12 * l34);
-    cx<double> v12 = loop2_block(O, N, m, 0, 1, t1, t1, lds);
-    cx<double> v34 = loop2_block(O, N, m, 2, 3, t0, t0, lds);
-    d1 = d1 + (1.0 / (m2 * m2)) * (v12 * v34);
-    d2 = d2 + (1.0 / m4) * loop4_block(O, N, m, t0, t1, t1, t0, M1, M2, lds);
-    d3 = d3 + (1.0 / m4) * loop4_block(O, N, m, t1, t1, t0, t0, M1, M2, lds);
-  }
-  if (threadIdx.x == 0) {
-    const double it = 1.0 / T;
-    diag[2 * (0 * T + dt)] = it * d0.re;
-    diag[2 * (0 * T + dt) + 1] = it * d0.im;
-    diag[2 * (1 * T + dt)] = it * d1.re;
-    diag[2 * (1 * T + dt) + 1] = it * d1.im;
-    diag[2 * (2 * T + dt)] = it * d2.re;
-    diag[2 * (2 * T + dt) + 1] = it * d2.im;
-    diag[2 * (3 * T + dt)] = it * d3.re;
-    diag[2 * (3 * T + dt) + 1] = it * d3.im;
-  }
-  if (vac) {
-    cx<double> v = loop2_block(O, N, m, 0, 1, dt, dt, lds);
-    if (threadIdx.x == 0) {
-      vac[2 * dt] = v.re / m2;
-      vac[2 * dt + 1] = v.im / m2;
+  double2* out = (double2*)w + ((size_t)k * T + t) * m * m;
+  double v[2] = {0.0, 0.0};
+  for (int e = threadIdx.x; e < m * m; e += 256) {
+    const int i = e / m, j = e % m;
+    if (k >= 4) {  // the loop's second factor, transposed, and its trace with the first
+      const double2 x = A[e], y = B[j * (m + 1) + i];
+      out[e] = y;
+      v[0] += x.x * y.x - x.y * y.y;
+      v[1] += x.x * y.y + x.y * y.x;
+      continue;
     }
+    // outputs of a row (P, R) or of a column (Q, S: stored transposed) are consecutive threads
+    const int r = k < 2 ? i : j, c = k < 2 ? j : i;
+    double2 s = make_double2(0.0, 0.0);
+    for (int l = 0; l < m; ++l) {
+      const double2 x = A[r * m + l], y = B[l * (m + 1) + c];
+      s.x += x.x * y.x - x.y * y.y;
+      s.y += x.x * y.y + x.y * y.x;
+    }
+    out[e] = s;
+  }
+  if (k >= 4) {
+    block_sum_n<2, 256>(v);
+    if (threadIdx.x < 2) loops[2 * ((size_t)(k - 4) * T + t) + threadIdx.x] = threadIdx.x == 0 ? v[0] : v[1];
   }
 }
 
-void launch_pipi(int T, int n, const double* O, double* diag, double* vac, hipStream_t s) {
-  hipLaunchKernelGGL(k_pipi, dim3(T), dim3(256), 0, s, T, n, O, diag, vac);
+// one block per dt, waves over t0
+constexpr int PIPI_WAVES = 16;
+__global__ __launch_bounds__(64 * PIPI_WAVES) void k_pipi(int T, int N, const double* O, const double* w,
+                                                         const double* loops, double* diag, double* vac) {
+  __shared__ double red[PIPI_WAVES][8];
+  const int dt = blockIdx.x, m = N / 4, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const size_t mm = (size_t)m * m;
+  const double2 *W = (const double2*)w, *Oc = (const double2*)O;
+  const double2 *v12 = (const double2*)loops, *v34 = v12 + T;
+  double d[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int t0 = wv; t0 < T; t0 += PIPI_WAVES) {
+    const int t1 = (t0 + dt) % T;
+    double v[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // L12, L34, the two 4-fold traces
+    auto add = [&](int k, const double2& x, const double2& y) {
+      v[2 * k] += x.x * y.x - x.y * y.y;
+      v[2 * k + 1] += x.x * y.y + x.y * y.x;
+    };
+    for (int e = lane; e < (int)mm; e += 64) {
+      const int i = e / m, j = e % m;
+      add(0, Oc[((size_t)t1 * N + i) * N + m + j], W[(4 * (size_t)T + t0) * mm + e]);
+      add(1, Oc[((size_t)t1 * N + 2 * m + i) * N + 3 * m + j], W[(5 * (size_t)T + t0) * mm + e]);
+      add(2, W[(size_t)t0 * mm + e], W[(2 * (size_t)T + t1) * mm + e]);
+      add(3, W[((size_t)T + t1) * mm + e], W[(3 * (size_t)T + t0) * mm + e]);
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = wave_sum(v[k]);
+    const double2 x = v12[t1], y = v34[t0];
+    d[0] += v[0] * v[2] - v[1] * v[3];
+    d[1] += v[0] * v[3] + v[1] * v[2];
+    d[2] += x.x * y.x - x.y * y.y;
+    d[3] += x.x * y.y + x.y * y.x;
+#pragma unroll
+    for (int k = 4; k < 8; ++k) d[k] += v[k];
+  }
+  if (lane == 0)
+#pragma unroll
+    for (int k = 0; k < 8; ++k) red[wv][k] = d[k];
+  __syncthreads();
+  if (threadIdx.x < 8) {
+    double s = 0.0;
+    for (int k = 0; k < PIPI_WAVES; ++k) s += red[k][threadIdx.x];
+    const double m4 = (double)mm * (double)mm;
+    diag[2 * ((size_t)(threadIdx.x / 2) * T + dt) + threadIdx.x % 2] = s / m4 / T;
+  }
+  if (vac && threadIdx.x == 0) {
+    vac[2 * dt] = v12[dt].x / (double)mm;
+    vac[2 * dt + 1] = v12[dt].y / (double)mm;
+  }
+}
+
+size_t pipi_work(int T, int n) { return (size_t)T * (6 * (size_t)(n / 4) * (n / 4) + 2); }
+
+void launch_pipi(int T, int n, const double* O, double* work, double* diag, double* vac, hipStream_t s) {
+  double* loops = work + 2 * (size_t)T * 6 * (n / 4) * (n / 4);
+  hipLaunchKernelGGL(k_pipi_products, dim3((unsigned)T, 6), dim3(256), 0, s, T, n, O, work, loops);
+  hipLaunchKernelGGL(k_pipi, dim3((unsigned)T), dim3(64 * PIPI_WAVES), 0, s, T, n, O, work, loops, diag, vac);
 }
 
 }  // namespace a2a
