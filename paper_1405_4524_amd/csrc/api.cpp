@@ -1363,7 +1363,7 @@ static int fill_geo(Ctx* c, const a2a_geom* geom, int nrhs, int t_src, Geo* g) {
   if (geom_to_geo(geom, g)) return c->fail(A2A_EINVAL, "bad lattice geometry");
   if (nrhs < 1) return c->fail(A2A_EINVAL, "nrhs must be positive");
   if (t_src < 0 || t_src >= g->T) return c->fail(A2A_EINVAL, "source timeslice out of range");
-  // M = 12 X Y Z rows and columns of the fill: (M / 64)^2 tiles must fit one launch
+  // M = 12 X Y Z rows and columns of the fill: (M / 32)^2 tiles must fit one launch
   if (12LL * g->X * g->Y * g->Z > (1LL << 21)) return c->fail(A2A_EINVAL, "timeslice too large for the fill");
   return A2A_OK;
 }
@@ -1380,14 +1380,12 @@ extern "C" int a2a_fill_propagator_dev(a2a_ctx* h, const a2a_geom* geom, const d
   FillArgs a{};
   a.P[0] = sol + 2 * t * M;
   a.Q[0] = src + 2 * t_src * M;
-  a.pm = a.qm = 1;
   a.pk = a.qk = col;
   a.M = a.N = (int)M;
   a.K = nrhs;
   a.scale = 1.0 / nrhs;
   a.out = S;
   a.om = M;
-  a.on = 1;
   a.dagger = dagger != 0;
   launch_fill(a, 1, c->stream);
   A2A_HIP(c, hipGetLastError());
@@ -1408,7 +1406,6 @@ extern "C" int a2a_contract_fill_2pt_dev(a2a_ctx* h, const a2a_geom* geom, const
   a.P[1] = sol2;
   a.Q[0] = src1 + 2 * t_src * M;
   a.Q[1] = src2 + 2 * t_src * M;
-  a.pm = a.qm = 1;
   a.pk = a.qk = col;
   a.pz = M;  // one sink timeslice per grid row
   a.M = a.N = (int)M;
