@@ -249,64 +249,68 @@ HD int brick_site(const Geo& g, int p) {
   return (((it * bt + rt) * g.Z + iz * bz + rz) * g.Y + iy * by + ry) * g.Xh + ix * bxh + rx;
 }
 
-// Position of a wave's sweep: brick origin and position inside the brick (the order of
-// brick_site<true>: y fastest, then x, z, t, bricks in lexicographic order).  Stepped by carries:
-// finding each position with integer divisions took half of the ~470 instructions a (site, tile) item
-// issued, and a wave issues one instruction every four to five cycles whatever else the chip does.
-struct SweepCursor {
-  int X0, Y0, Z0, T0, rx, ry, rz, rt;
-  HD void init(const Geo& g, int p) {
-    const int B = g.bxh * g.by * g.bz * g.bt;
-    int br = p / B, r = p - br * B;
-    ry = r % g.by;
-    r /= g.by;
+// Position of a wave's sweep over pairs of output sites in rows y and y + 1 (y even) at the same x_h: row
+// pairs run along x, then y, z, t inside a brick, bricks in lexicographic order (a brick with an odd y
+// extent counts as twice as tall, which tiles the lattice too).  Stepped by carries: finding each position
+// with integer divisions took half of the instructions of a site.
+struct PairCursor {
+  int by, X0, Y0, Z0, T0, rx, ry, rz, rt;
+  HD void init(const Geo& g, int q) {
+    by = g.by % 2 ? 2 * g.by : g.by;
+    const int B = g.bxh * (by / 2) * g.bz * g.bt;
+    int br = q / B, r = q - br * B;
     rx = r % g.bxh;
     r /= g.bxh;
+    ry = r % (by / 2) * 2;
+    r /= by / 2;
     rz = r % g.bz;
     rt = r / g.bz;
-    const int nbx = g.Xh / g.bxh, nby = g.Y / g.by, nbz = g.Z / g.bz;
+    const int nbx = g.Xh / g.bxh, nby = g.Y / by, nbz = g.Z / g.bz;
     X0 = (br % nbx) * g.bxh;
     br /= nbx;
-    Y0 = (br % nby) * g.by;
+    Y0 = (br % nby) * by;
     br /= nby;
     Z0 = (br % nbz) * g.bz;
     T0 = br / nbz * g.bt;
   }
-  HD void next(const Geo& g) {
-    if (++ry < g.by) return;
-    ry = 0;
-    if (++rx < g.bxh) return;
+  // true: the next pair is not the one behind this one along x
+  HD bool next(const Geo& g) {
+    if (++rx < g.bxh) return false;
     rx = 0;
-    if (++rz < g.bz) return;
+    if ((ry += 2) < by) return true;
+    ry = 0;
+    if (++rz < g.bz) return true;
     rz = 0;
-    if (++rt < g.bt) return;
+    if (++rt < g.bt) return true;
     rt = 0;
-    if ((X0 += g.bxh) < g.Xh) return;
+    if ((X0 += g.bxh) < g.Xh) return true;
     X0 = 0;
-    if ((Y0 += g.by) < g.Y) return;
+    if ((Y0 += by) < g.Y) return true;
     Y0 = 0;
-    if ((Z0 += g.bz) < g.Z) return;
+    if ((Z0 += g.bz) < g.Z) return true;
     Z0 = 0;
     T0 += g.bt;
+    return true;
   }
 };
 
-// cb indices of the eight neighbours (d = 2 mu + f, f = 0 forward, 1 backward) of the cursor's site of
-// parity par; returns the site's own
-HD int cursor_neighbours(const Geo& g, const SweepCursor& c, int par, int nb[8]) {
-  const int xh = c.X0 + c.rx, y = c.Y0 + c.ry, z = c.Z0 + c.rz, t = c.T0 + c.rt;
+// Site r (0 or 1) of a pair, for outputs of parity par.  Site 0 lies in the row in which x = 2 x_h, site 1 in
+// the other.  With P_j and Q_j the inputs in site 0's and site 1's row at x_h = j, site 0's x neighbours are
+// P_i (forward) and P_{i-1}, site 1's Q_{i+1} (forward) and Q_i, and the y neighbour of each in the other's
+// row is Q_i and P_i.  nb: the y neighbour outside the pair (forward if *up) and those in z and t (forward,
+// backward); row: x_h = 0 of the site's row.
+HD int pair_site(const Geo& g, const PairCursor& c, int par, int r, int nb[5], int* up, int* row) {
+  const int z = c.Z0 + c.rz, t = c.T0 + c.rt;
+  const int u = ((z + t + par) & 1) ^ r, y = c.Y0 + c.ry + u;
   const int sy = g.Xh, sz = g.Xh * g.Y, st = g.Xh * g.Y * g.Z;
-  const int site = t * st + z * sz + y * sy + xh;
-  const int x = 2 * xh + ((y + z + t + par) & 1);
-  const int row = site - xh;
-  nb[0] = row + ((x + 1 == g.X ? 0 : x + 1) >> 1);
-  nb[1] = row + ((x == 0 ? g.X - 1 : x - 1) >> 1);
-  nb[2] = site + (y == g.Y - 1 ? sy - sz : sy);
-  nb[3] = site + (y == 0 ? sz - sy : -sy);
-  nb[4] = site + (z == g.Z - 1 ? sz - st : sz);
-  nb[5] = site + (z == 0 ? st - sz : -sz);
-  nb[6] = site + (t == g.T - 1 ? st - g.hv : st);
-  nb[7] = site + (t == 0 ? g.hv - st : -st);
+  *row = t * st + z * sz + y * sy;
+  *up = u;
+  const int site = *row + c.X0 + c.rx;
+  nb[0] = u ? site + (y == g.Y - 1 ? sy - sz : sy) : site + (y == 0 ? sz - sy : -sy);
+  nb[1] = site + (z == g.Z - 1 ? sz - st : sz);
+  nb[2] = site + (z == 0 ? st - sz : -sz);
+  nb[3] = site + (t == g.T - 1 ? st - g.hv : st);
+  nb[4] = site + (t == 0 ? g.hv - st : -st);
   return site;
 }
 

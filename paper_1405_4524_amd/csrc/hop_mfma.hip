@@ -8,7 +8,7 @@
 // direction d (the link, or the daggered backward link, with the fermion boundary sign).
 // Every RHS of a group sees the same matrix, so one wavefront takes one site at a time and
 // multiplies the matrix with the 192 x 16 block of neighbour data of each 16-lane tile on the
-// matrix cores: v_mfma_f32_16x16x32 over 2 row tiles (24 rows + 8 unused) x 6 K steps.  The
+// matrix cores: v_mfma_f32_16x16x32 over 2 row tiles (24 rows + 8 unused) x 7 K steps.  The
 // clover term A_x psi(x) is one more K step (24 columns + 8 zero columns).  The inverse-clover
 // epilogue is a second product after a register -> LDS -> register transpose of the hop result
 // (which rounds that intermediate to the storage format).  Calls with an axpy term (aux1) use
@@ -181,43 +181,49 @@ __device__ __forceinline__ void wave_lds_sync() {
 
 }  // namespace
 
-// Data one 16-lane tile of one site needs, each as the lane's 16 bytes in the B-fragment layout
-// (chunk gq of its RHS; lanes gq = 3 repeat chunk 0): the six K steps of neighbour data, the
-// clover input (EPI_CLOV) and the other operand of the ALPHA reduction (OMEGA's is the clover
-// input).  One 16-byte load per lane and operand keeps the count of memory instructions, which
-// is what the address units spend their cycles on, low.
-struct TileIn {
-  uint4 SD;  // this lane's 16 bytes of the site's links (lanes 0..17) and clover (18..35); tile 0 only
-  uint4 B[6];
-  uint4 Bc;
-  uint4 Bx;
-  int site;
+// Data one site needs beside its x neighbours and the y neighbour it shares with its pair, for each 16-lane
+// tile the lane's 16 bytes in the B-fragment layout (chunk gq of its RHS; lanes gq = 3 repeat chunk 0): the
+// other y neighbour, the three K steps of z and t neighbours, the clover input (EPI_CLOV) and the other
+// operand of the ALPHA reduction (OMEGA's is the clover input).  One 16-byte load per lane and operand keeps
+// the count of memory instructions, which is what the address units spend their cycles on, low.
+template <int NT>
+struct SiteIn {
+  uint4 SD;  // this lane's 16 bytes of the site's links (lanes 0..17) and clover (18..35)
+  uint4 O[NT];
+  uint4 Z[NT][3];
+  uint4 Bc[NT];
+  uint4 Bx[NT];
+  int site, up;  // up: O is the forward y neighbour
 };
 
-// A block takes all NT lane tiles of a group over a 1 / nsub part of BS sites of a 4D brick of the
-// lattice (the whole x row, then y, z, t extents), so that most neighbours of a block's sites
-// are sites of the same block; bricks follow in lexicographic order.  A wave's items are
-// (site, lane tile) pairs, tiles inner: the site's matrix is built once and applied to every
-// tile of the group (one build per site instead of one per site and tile: 10% faster Schur
-// operator at 48 RHS, results bitwise unchanged).  Inside a brick the sweep runs y fastest,
-// then x, then z and t: the waves of a block take (z, t) planes of the brick at the same
-// (x, y) positions, so that a neighbour spinor is used by the z and t neighbours of other
-// waves at about the same time, by its y neighbours two positions apart and by its x
-// neighbours a few positions apart, while it is still in the L2 (x fastest put the y uses a
-// whole row apart and cost a quarter more L2 misses).  Blocks are not grouped by XCD.  The
-// links, clover and neighbour data of item i + 2 are requested while item i is computed (a ring
-// of three register buffers), and the matrix fragments are read from LDS right before their
-// products.  The tile of an item and its buffer are compile-time (the sweep is unrolled over
-// lcm(3, NT) items), so the neighbour addresses are found once per site and a tile is an
-// immediate offset.
-
+// A block takes all NT lane tiles of a group over a 1 / nsub part of BS sites of 4D bricks of the lattice
+// (the whole x row, then y, z, t extents), so that most neighbours of a block's sites are sites of the same
+// block.  A wave builds a site's matrix and applies it to every tile of the group.
+//
+// What bounds it: gathered lines that miss the CU's vector L1.  At 48 RHS a CU has about 68 128-byte requests
+// to its L2 in flight, 490 cycles each, while address, matrix and LDS units idle half the time, so the count
+// of gathered lines sets the time (with every gather in one L2-resident line set the pair below took 2.9 ms).
+// A wave therefore sweeps pairs of output sites in adjacent y rows along x: each new pair needs one new
+// input per row, the inputs behind them and each other's row stay in registers, and a site gathers six
+// spinors instead of eight.  To share registers across K steps, each x and y direction is a K step of its own
+// (three chunks and a zero chunk; seven K steps instead of six).  The fragments of the matrix are read from
+// LDS once per K step for all tiles, and each operand's registers are refilled with the next site's data as
+// soon as its products are issued, so a site's requests are in flight for a whole site.  Schur pair, 32^3x64,
+// 48 RHS: one tile at a time with eight gathers 4080 us, tiles sharing fragments 3945, pairs 3641, pairs in
+// compact cells of bricks 3557 (its reads and writes alone take 2.6 ms at the rate of a
+// copy); 24^3x48, 32 RHS: 954, 933, 910, 895; 16^3x32, 16 RHS: 114, 114, 113, 111.
+//
+// One tile (DEPTH 2: requests two sites ahead) and two tiles fit three waves per SIMD, three tiles two; two
+// tiles two sites ahead at two waves take 86 us for 73 at 12^3x24 and the same on larger lattices.
 template <class P, int EPI, int RED, int NT>
-__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_hop_mfma(HopMArgs a) {
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(NT == 3 ? 2 : 3))) void k_hop_mfma(HopMArgs a) {
   using S = typename P::S;
   using M = MM<S>;
+  constexpr int DEPTH = NT == 1 ? 2 : 1;  // sites requested ahead
   __shared__ uint4 tbl[WAVES][24][TROW];  // the site's matrix
-  __shared__ uint4 stg[WAVES][64];        // the site's links (chunks 0..17) and clover (18..35)
-  __shared__ uint4 trb[WAVES][16][TRW];   // register-layout transposes, one row per RHS lane
+  // register-layout transposes, one row per RHS lane; before them the site's links (chunks 0..17) and
+  // clover (18..35)
+  __shared__ uint4 trb[WAVES][16][TRW];
 
   const int2 tile = a.tiles[blockIdx.x];  // {group, site block}
   const ILGroupDev& grp = a.groups[tile.x];
@@ -230,6 +236,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(3, 3))) void
   const int n = lane & 15, gq = lane >> 4;
   uint4(*T)[TROW] = tbl[w];
   uint2* tr2 = (uint2*)&trb[w][n][0];  // this lane's transpose row as 8-byte pieces
+  uint4* stg = &trb[w][0][0];
 
   // ---- lane constants: matrix-building role (d, s, c') and the four spin-column variants
   const int bd = lane & 7, bs = (lane >> 3) & 3, bc = lane >> 5;
@@ -301,9 +308,9 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(3, 3))) void
   const bool sd_clover = EPI != 0 && sdl >= 18;
   const char* sd_base = sd_clover ? cf + (sdl - 18) * 16 : hl + (sdl % 18) * 16;
   auto build = [&](const uint4& SD) {
-    stg[w][lane] = SD;
+    stg[lane] = SD;
     wave_lds_sync();
-    const uint32_t* st32 = (const uint32_t*)&stg[w][0];
+    const uint32_t* st32 = (const uint32_t*)stg;
     uint32_t L[9];
 #pragma unroll
     for (int j = 0; j < 9; ++j) L[j] = st32[bd * 9 + j];
@@ -332,166 +339,257 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     }
   };
 
-  // Prefetch cursor: site ps of the wave's range, its neighbour addresses (found with tile 0, used
-  // by every tile).  Loads are unconditional (past the range the last site is loaded again), so the
-  // number of memory operations in flight is the same on every path and the waits on them stay exact.
   constexpr long long SITE = NT * 768;  // bytes of a site in a group's vector
-  unsigned hoff[3];                     // chunk (4 kt + gq) % 3 of this lane's RHS, kt = 0..2 (3..5 repeat)
+  unsigned hoff[3];                     // chunk (4 kt + gq) % 3 of this lane's RHS, kt = 0..2
 #pragma unroll
   for (int t = 0; t < 3; ++t) hoff[t] = ((4 * t + gq) % 3) * 256 + n * 16;
   const int own = ochunk * 256 + n * 16;
-  SweepCursor cu;
-  int ps = 0, psite = 0;
-  const char* nba[6];
-  auto locate = [&]() {
-    int nb[8];
-    psite = __builtin_amdgcn_readfirstlane(cursor_neighbours(g, cu, po, nb));
-    // chunk 4 kt + gq belongs to direction (4 kt + gq) / 3
-    const int nbs[6] = {gq >= 3 ? nb[1] : nb[0], gq >= 2 ? nb[2] : nb[1], gq >= 1 ? nb[3] : nb[2],
-                        gq >= 3 ? nb[5] : nb[4], gq >= 2 ? nb[6] : nb[5], gq >= 1 ? nb[7] : nb[6]};
+  // fragment columns of the x and y K steps: the direction's three chunks and a zero chunk
+  const int xcol = gq < 3 ? gq : TCLO + 3, xstep = gq < 3 ? 3 : 0;
+
+  // Loads are unconditional (past the range the last pair is loaded again), so that the number of memory
+  // operations in flight is the same on every path and the waits on them stay exact; only the two extra
+  // inputs of a pair that starts a row are requested under a branch.
+  auto in4 = [&](int site, int t) { return gld4(vin + (site * SITE + t * 768) + own); };
+  auto own4 = [&](const char* v, int site, int t) { return gld4nt(v + (site * SITE + t * 768) + own); };
+  PairCursor cu;  // the pair requested last
+  struct Row {
+    int site, nb[5], up, row;
+  };
+  auto locate = [&](int r) {
+    Row w;
+    w.site = pair_site(g, cu, po, r, w.nb, &w.up, &w.row);
+    return w;
+  };
+  auto wrap = [&](int j) { return j < 0 ? j + g.Xh : j >= g.Xh ? j - g.Xh : j; };
+  // One output site.  S: its data, refilled for the site `to`; xp, xm, tw: its forward and backward x
+  // neighbours and the y neighbour in the pair's other row; xm is refilled with input x_to.  At the end of
+  // a row xp and tw are refilled too (xp_to, tw_to).
+  auto step = [&](SiteIn<NT>& r, uint4* xp, uint4* xm, uint4* tw, const Row& to, int x_to, bool fresh, int xp_to,
+                  int tw_to) {
+    const int site = r.site, up = r.up;
+    const int nbs[3] = {gq >= 3 ? to.nb[2] : to.nb[1], gq >= 2 ? to.nb[3] : to.nb[2], gq >= 1 ? to.nb[4] : to.nb[3]};
+    const char* zad[3];
 #pragma unroll
-    for (int kt = 0; kt < 6; ++kt) {
-      unsigned h = hoff[kt % 3];
+    for (int k = 0; k < 3; ++k) {
+      unsigned h = hoff[k];
       asm volatile("" : "+v"(h));  // keeps the 64-bit sums vin + hoff out of registers of their own (they spilled)
-      nba[kt] = vin + ((unsigned long long)(unsigned)nbs[kt] * (unsigned)SITE + h);
+      zad[k] = vin + ((unsigned long long)(unsigned)nbs[k] * (unsigned)SITE + h);
     }
-  };
-  auto prefetch = [&](TileIn& dst, auto tile_c) {
-    constexpr int nt = decltype(tile_c)::value;
-    dst.site = psite;
-    if (nt == 0) dst.SD = gld4(sd_base + (size_t)psite * 288);
-#pragma unroll
-    for (int kt = 0; kt < 6; ++kt) dst.B[kt] = gld4(nba[kt] + nt * 768);
-    const long long at = psite * SITE + nt * 768;
-    if (EPI == 1 || EPI == 3) dst.Bc = gld4nt(vaux2 + at + own);
-    if (RED == RED_ALPHA) dst.Bx = gld4nt(vrh + at + own);
-    if (nt == NT - 1) {  // the site's last tile: on to the next site
-      if (ps + 1 < cnt) {
-        ++ps;
-        cu.next(g);
-      }
-      locate();
-    }
-  };
-  auto step = [&](TileIn& cur, TileIn& pf, auto cur_tile, auto pf_tile) {
-    constexpr int nt = decltype(cur_tile)::value;
-    const int site = cur.site;
-    if (nt == 0) build(cur.SD);  // this site's matrix, once for all its tiles
-    prefetch(pf, pf_tile);
-    __builtin_amdgcn_sched_barrier(0);  // keep the requests ahead of this item's work
+    r.site = to.site;
+    r.up = to.up;
+    build(r.SD);
+    r.SD = gld4(sd_base + (size_t)to.site * 288);
     wave_lds_sync();
-    f4v acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+    f4v acc0[NT], acc1[NT];
 #pragma unroll
-    for (int kt = 0; kt < 6; ++kt) {
-      acc0 = M::mma(T[frow0][4 * kt + gq], cur.B[kt], acc0);
-      acc1 = M::mma(T[frow1][4 * kt + gq], cur.B[kt], acc1);
-    }
-    float v0[4], v1[4];
+    for (int t = 0; t < NT; ++t) acc0[t] = acc1[t] = f4v{0.f, 0.f, 0.f, 0.f};
+    uint4 A0 = T[frow0][xcol], A1 = T[frow1][xcol];
+    // K step k's products with B, the fragments of column c after it requested first
+    auto products = [&](auto B, int c) {
+      const uint4 a0 = A0, a1 = A1;
+      if (c >= 0) {
+        A0 = T[frow0][c];
+        A1 = T[frow1][c];
+      }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      v0[r] = gam * acc0[r];
-      v1[r] = gam * acc1[r];
+      for (int t = 0; t < NT; ++t) {
+        acc0[t] = M::mma(a0, B(t), acc0[t]);
+        acc1[t] = M::mma(a1, B(t), acc1[t]);
+      }
+    };
+    products([&](int t) { return xp[t]; }, xcol + xstep);
+    products([&](int t) { return xm[t]; }, xcol + (up ? 3 : 2) * xstep);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) xm[t] = in4(x_to, t);
+    __builtin_amdgcn_sched_barrier(0);  // keeps the requests here
+    products([&](int t) { return tw[t]; }, xcol + (up ? 2 : 3) * xstep);
+    if (fresh) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        tw[t] = in4(tw_to, t);
+        xp[t] = in4(xp_to, t);
+      }
     }
+    products([&](int t) { return r.O[t]; }, 12 + gq);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) r.O[t] = in4(to.nb[0], t);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {  // the clover block follows the last K step
+      products([&](int t) { return r.Z[t][k]; }, k < 2 || EPI != 0 ? 12 + 4 * (k + 1) + gq : -1);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) r.Z[t][k] = gld4(zad[k] + t * 768);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    float v0[NT][4], v1[NT][4];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        v0[t][q] = gam * acc0[t][q];
+        v1[t][q] = gam * acc1[t][q];
+      }
+    const f4v zero = {0.f, 0.f, 0.f, 0.f};
     if (EPI == 1) {
-      const f4v zero = {0.f, 0.f, 0.f, 0.f};
-      const f4v c0 = M::mma(T[frow0][TCLO + gq], cur.Bc, zero), c1 = M::mma(T[frow1][TCLO + gq], cur.Bc, zero);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        v0[r] += cbv * c0[r];
-        v1[r] += cbv * c1[r];
+      for (int t = 0; t < NT; ++t) {
+        const f4v c0 = M::mma(A0, r.Bc[t], zero), c1 = M::mma(A1, r.Bc[t], zero);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          v0[t][q] += cbv * c0[q];
+          v1[t][q] += cbv * c1[q];
+        }
       }
     }
     if (EPI == 2 || EPI == 3) {  // o = A^{-1} (.): transpose the rounded result through LDS, second product
-      tr2[gq] = make_uint2(M::pack2(v0[0], v0[1]), M::pack2(v0[2], v0[3]));
-      tr2[4 + gq] = gq < 2 ? make_uint2(M::pack2(v1[0], v1[1]), M::pack2(v1[2], v1[3])) : make_uint2(0, 0);
-      wave_lds_sync();
-      const uint4 B2 = trb[w][n][gq];
-      wave_lds_sync();
-      const f4v zero = {0.f, 0.f, 0.f, 0.f};
-      const f4v c0 = M::mma(T[frow0][TCLO + gq], B2, zero), c1 = M::mma(T[frow1][TCLO + gq], B2, zero);
+      uint4 B2[NT];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        v0[r] = c0[r];
-        v1[r] = c1[r];
+      for (int t = 0; t < NT; ++t) {
+        tr2[gq] = make_uint2(M::pack2(v0[t][0], v0[t][1]), M::pack2(v0[t][2], v0[t][3]));
+        tr2[4 + gq] = gq < 2 ? make_uint2(M::pack2(v1[t][0], v1[t][1]), M::pack2(v1[t][2], v1[t][3])) : make_uint2(0, 0);
+        wave_lds_sync();
+        B2[t] = trb[w][n][gq];
+        wave_lds_sync();
+      }
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const f4v c0 = M::mma(A0, B2[t], zero), c1 = M::mma(A1, B2[t], zero);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          v0[t][q] = c0[q];
+          v1[t][q] = c1[q];
+        }
       }
     }
     if (EPI == 3) {  // o = aux2 + A^{-1} (.): the site's aux2 chunk to output rows through LDS
-      trb[w][n][gq] = cur.Bc;
-      wave_lds_sync();
-      const uint2 a0 = tr2[gq], a1 = tr2[4 + gq];
-      wave_lds_sync();
-      v0[0] += M::lo(a0.x);
-      v0[1] += M::hi(a0.x);
-      v0[2] += M::lo(a0.y);
-      v0[3] += M::hi(a0.y);
-      v1[0] += M::lo(a1.x);
-      v1[1] += M::hi(a1.x);
-      v1[2] += M::lo(a1.y);
-      v1[3] += M::hi(a1.y);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        trb[w][n][gq] = r.Bc[t];
+        wave_lds_sync();
+        const uint2 x0 = tr2[gq], x1 = tr2[4 + gq];
+        wave_lds_sync();
+        v0[t][0] += M::lo(x0.x);
+        v0[t][1] += M::hi(x0.x);
+        v0[t][2] += M::lo(x0.y);
+        v0[t][3] += M::hi(x0.y);
+        v1[t][0] += M::lo(x1.x);
+        v1[t][1] += M::hi(x1.x);
+        v1[t][2] += M::lo(x1.y);
+        v1[t][3] += M::hi(x1.y);
+      }
     }
     // rows 16 m + 4 gq .. +3 of row tile m, rounded to the storage format
-    const uint2 q0 = make_uint2(M::pack2(v0[0], v0[1]), M::pack2(v0[2], v0[3]));
-    const uint2 q1 = make_uint2(M::pack2(v1[0], v1[1]), M::pack2(v1[2], v1[3]));
-    if (RED == RED_ALPHA || RED == RED_OMEGA) {  // over the values as stored
-      trb[w][n][gq] = RED == RED_ALPHA ? cur.Bx : cur.Bc;  // the partner, to output rows
-      wave_lds_sync();
-      const uint2 xr0 = tr2[gq], xr1 = tr2[4 + gq];
-      wave_lds_sync();
-      float r0 = 0.f, r1 = 0.f, r2 = 0.f;
+    uint2 q0[NT], q1[NT];
 #pragma unroll
-      for (int m = 0; m < 2; ++m) {
-        if (m == 1 && gq >= 2) continue;
-        const uint2 q = m ? q1 : q0;
-        const uint2 x = m ? xr1 : xr0;
-        const float o0 = M::lo(q.x), o1 = M::hi(q.x), o2 = M::lo(q.y), o3 = M::hi(q.y);
-        const float x0 = M::lo(x.x), x1 = M::hi(x.x), x2 = M::lo(x.y), x3 = M::hi(x.y);
-        if (RED == RED_ALPHA) {  // (rhat, o)
-          r0 += x0 * o0 + x1 * o1 + x2 * o2 + x3 * o3;
-          r1 += x0 * o1 - x1 * o0 + x2 * o3 - x3 * o2;
-        } else {  // (o, aux2), |o|^2
-          r0 += o0 * x0 + o1 * x1 + o2 * x2 + o3 * x3;
-          r1 += o0 * x1 - o1 * x0 + o2 * x3 - o3 * x2;
-          r2 += o0 * o0 + o1 * o1 + o2 * o2 + o3 * o3;
-        }
-      }
-      // a select, not a product with 0 or 1: an idle lane's column holds whatever its memory
-      // held, and 0 * NaN would reach the partial sums of the same lane in the other tiles
-      const bool keep = (used >> nt) & 1;
-      red[nt][0] += keep ? r0 : 0.f;
-      red[nt][1] += keep ? r1 : 0.f;
-      red[nt][2] += keep ? r2 : 0.f;
+    for (int t = 0; t < NT; ++t) {
+      q0[t] = make_uint2(M::pack2(v0[t][0], v0[t][1]), M::pack2(v0[t][2], v0[t][3]));
+      q1[t] = make_uint2(M::pack2(v1[t][0], v1[t][1]), M::pack2(v1[t][2], v1[t][3]));
     }
+    if (RED == RED_ALPHA || RED == RED_OMEGA) {  // over the values as stored
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        trb[w][n][gq] = RED == RED_ALPHA ? r.Bx[t] : r.Bc[t];  // the partner, to output rows
+        wave_lds_sync();
+        const uint2 xr0 = tr2[gq], xr1 = tr2[4 + gq];
+        wave_lds_sync();
+        float r0 = 0.f, r1 = 0.f, r2 = 0.f;
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          if (m == 1 && gq >= 2) continue;
+          const uint2 q = m ? q1[t] : q0[t];
+          const uint2 x = m ? xr1 : xr0;
+          const float o0 = M::lo(q.x), o1 = M::hi(q.x), o2 = M::lo(q.y), o3 = M::hi(q.y);
+          const float x0 = M::lo(x.x), x1 = M::hi(x.x), x2 = M::lo(x.y), x3 = M::hi(x.y);
+          if (RED == RED_ALPHA) {  // (rhat, o)
+            r0 += x0 * o0 + x1 * o1 + x2 * o2 + x3 * o3;
+            r1 += x0 * o1 - x1 * o0 + x2 * o3 - x3 * o2;
+          } else {  // (o, aux2), |o|^2
+            r0 += o0 * x0 + o1 * x1 + o2 * x2 + o3 * x3;
+            r1 += o0 * x1 - o1 * x0 + o2 * x3 - o3 * x2;
+            r2 += o0 * o0 + o1 * o1 + o2 * o2 + o3 * o3;
+          }
+        }
+        // a select, not a product with 0 or 1: an idle lane's column holds whatever its memory
+        // held, and 0 * NaN would reach the partial sums of the same lane in the other tiles
+        const bool keep = (used >> t) & 1;
+        red[t][0] += keep ? r0 : 0.f;
+        red[t][1] += keep ? r1 : 0.f;
+        red[t][2] += keep ? r2 : 0.f;
+      }
+    }
+    if (EPI == 1 || EPI == 3)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) r.Bc[t] = own4(vaux2, to.site, t);
+    if (RED == RED_ALPHA)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) r.Bx[t] = own4(vrh, to.site, t);
     // to the storage layout through LDS: one 16-byte store per lane (idle lanes write their own
     // unread lane slots; lanes gq = 3 repeat the chunk-0 store of lane gq = 0)
-    tr2[gq] = q0;
-    tr2[4 + gq] = q1;
-    wave_lds_sync();
-    const uint4 ob = trb[w][n][ochunk];
-    wave_lds_sync();
-    gst4nt(vout + (site * SITE + nt * 768) + own, ob);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      tr2[gq] = q0[t];
+      tr2[4 + gq] = q1[t];
+      wave_lds_sync();
+      gst4nt(vout + (site * SITE + t * 768) + own, trb[w][n][ochunk]);
+      wave_lds_sync();
+    }
   };
 
   if (cnt > 0) {
-    TileIn R[3];
-    cu.init(g, s0);
-    locate();
-    prefetch(R[0], std::integral_constant<int, 0>{});
-    prefetch(R[1], std::integral_constant<int, 1 % NT>{});
-    int left = cnt * NT;  // items
-#define A2A_STEP(i)                                                                                        \
-  step(R[(i) % 3], R[((i) + 2) % 3], std::integral_constant<int, (i) % NT>{}, std::integral_constant<int, ((i) + 2) % NT>{}); \
-  if (--left == 0) break
-    for (;;) {
-      A2A_STEP(0);
-      A2A_STEP(1);
-      A2A_STEP(2);
-      if constexpr (NT == 2) {  // tiles repeat every two items, buffers every three
-        A2A_STEP(3);
-        A2A_STEP(4);
-        A2A_STEP(5);
+    SiteIn<NT> sites[DEPTH];
+    uint4 ip[2][NT], iq[2][NT];  // inputs in the rows of site 0 and site 1
+    cu.init(g, s0 >> 1);
+    int left = cnt >> 1, ahead = left;  // pairs to compute, pairs to request (this one included)
+    auto fill = [&](SiteIn<NT>& r, const Row& to) {
+      r.site = to.site;
+      r.up = to.up;
+      r.SD = gld4(sd_base + (size_t)to.site * 288);
+      const int nbs[3] = {gq >= 3 ? to.nb[2] : to.nb[1], gq >= 2 ? to.nb[3] : to.nb[2], gq >= 1 ? to.nb[4] : to.nb[3]};
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        r.O[t] = in4(to.nb[0], t);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) r.Z[t][k] = gld4(vin + (nbs[k] * SITE + t * 768) + hoff[k]);
+        if (EPI == 1 || EPI == 3) r.Bc[t] = own4(vaux2, to.site, t);
+        if (RED == RED_ALPHA) r.Bx[t] = own4(vrh, to.site, t);
       }
+    };
+    {
+      const Row l = locate(0), m = locate(1);
+      const int i = cu.X0 + cu.rx;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        ip[0][t] = in4(l.row + i, t);
+        ip[1][t] = in4(l.row + wrap(i - 1), t);
+        iq[0][t] = in4(m.row + i, t);
+        iq[1][t] = in4(m.row + wrap(i + 1), t);
+      }
+      fill(sites[0], l);
+      if (DEPTH == 2) fill(sites[DEPTH - 1], m);
     }
-#undef A2A_STEP
+    // the two sites of a pair; ph: ip[ph], iq[ph] hold the inputs at the pair's own x_h, ip[ph ^ 1] the one
+    // behind, iq[ph ^ 1] the one ahead
+    auto pair = [&](auto ph_c) {
+      constexpr int ph = decltype(ph_c)::value;
+      const Row m0 = locate(1);
+      bool fresh = false;
+      if (ahead > 1) {
+        --ahead;
+        fresh = cu.next(g);
+      }
+      const Row l = locate(0), m = locate(1);
+      const int i = cu.X0 + cu.rx;
+      step(sites[0], ip[ph], ip[ph ^ 1], iq[ph], DEPTH == 2 ? l : m0, l.row + i, false, 0, 0);
+      step(sites[DEPTH - 1], iq[ph ^ 1], iq[ph], ip[ph], DEPTH == 2 ? m : l, m.row + wrap(i + 1), fresh, m.row + i,
+           l.row + wrap(i - 1));
+    };
+    for (;;) {
+      pair(std::integral_constant<int, 0>{});
+      if (--left == 0) break;
+      pair(std::integral_constant<int, 1>{});
+      if (--left == 0) break;
+    }
   }
 
   if (RED == RED_ALPHA || RED == RED_OMEGA) {
@@ -555,11 +653,14 @@ static void launch_mfma_p(const HopMArgs& a, int ntiles, int epi, hipStream_t s)
 }
 
 // A block's four waves sweep BS / nsub sites one after another, about half a microsecond each, so nsub
-// sets how many of the chip's ~768 resident blocks there are and how long the last of them run (Schur
-// pair, 16 sources: 8^3x16, 16 bricks, 199 us whole and 20 us in 16 parts; 16^3x32, 256 bricks, 199 us
-// whole, 107 in two and 113 in four; 28^3x56, 2401 bricks of which no 768 fit evenly, 48 sources, 3827 us
-// whole and 2891 in four; 32^3x64 is the same at one, two and four).
-int il_subblocks(int hv) { return (hv + BS - 1) / BS >= 128 ? 4 : 16; }
+// sets how many of the chip's ~512 resident blocks there are and how long the last of them run (Schur
+// pair, 16 sources: 8^3x16, 16 bricks, 199 us whole and 20 us in 16 parts; 16^3x32, 256 blocks, 199 us
+// whole, 107 in two and 113 in four; 48 sources: 248 in two, 229 in four; 24^3x48, 1296 blocks, 32 sources
+// 982 in two, 896 in four; 32^3x64, 4096 blocks, 48 sources 3537 in two, 3613 in four).
+int il_subblocks(int hv) {
+  const int nblk = (hv + BS - 1) / BS;
+  return nblk >= 2048 ? 2 : nblk >= 128 ? 4 : 16;
+}
 
 bool hop_mfma_supports(int prec, int inv, bool clov, int red, bool aux1) {
   if ((prec != 2 && prec != 3) || aux1) return false;

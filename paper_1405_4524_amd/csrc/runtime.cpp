@@ -86,19 +86,33 @@ void xcd_order(std::vector<int2>& tiles, bool enable) {
   tiles.swap(out);
 }
 
-// Matrix-core blocks {group, part} in brick order: each XCD takes runs of up to 16 consecutive bricks
-// with all their nsub parts, so that neighbouring bricks and the parts of one brick share an L2 (Schur
-// pair, 24^3x48 with 32 sources: 1263 us with bricks and parts dealt out one by one, 974 in runs; in
-// XCD slabs 988 there, but 10% slower than runs at 32^3x64, 4510 against 4096 us).
-static void xcd_runs(int group, int nblk, int nsub, std::vector<int2>& out) {
-  const int run = std::max(1, std::min(16, nblk / 8));
-  for (int b0 = 0; b0 < nblk; b0 += 8 * run)
-    for (int j = 0; j < run; ++j)
+// Matrix-core blocks {group, part}: blocks of BS sites are listed by cells of 4 x 2 x 2 bricks in y, z, t
+// (bricks in lexicographic order inside a cell) and each XCD takes runs of up to 16 of them with all their
+// nsub parts, so that neighbours in every direction and the parts of one brick share an L2; what is left
+// after the whole runs is dealt out evenly.  Schur pair, 24^3x48 with 32 sources: 1263 us with bricks and
+// parts dealt out one by one, 974 in lexicographic runs; 32^3x64 with 48: 4096 us in such runs, 10% more in
+// XCD slabs.  Cells against lexicographic runs, with the paired sweep: 16^3x32, 48 sources 250 -> 229 us,
+// 24^3x48, 32 sources 918 -> 896, 32^3x64, 48 sources 3633 -> 3613.
+static void xcd_runs(const Geo& g, int group, int nblk, int nsub, std::vector<int2>& out) {
+  const int B = g.bxh * g.by * g.bz * g.bt, nx = g.Xh / g.bxh, ny = g.Y / g.by, nz = g.Z / g.bz;
+  const int cy = (ny + 3) / 4, cz = (nz + 1) / 2, ct = (g.T / g.bt + 1) / 2;
+  std::vector<int> first(cy * cz * ct + 1, 0), list(nblk);
+  auto cell = [&](int b) {
+    const int br = (int)((long)b * BS / B) / nx, y = br % ny, z = br / ny % nz, t = br / ny / nz;
+    return (t / 2 * cz + z / 2) * cy + y / 4;
+  };
+  for (int b = 0; b < nblk; ++b) ++first[cell(b) + 1];
+  for (int c = 0; c < cy * cz * ct; ++c) first[c + 1] += first[c];
+  for (int b = 0; b < nblk; ++b) list[first[cell(b)]++] = b;
+  for (int b0 = 0; b0 < nblk;) {
+    const int rest = nblk - b0, n = std::min(rest, 128);  // of this round over the XCDs
+    const int run = n / 8, more = n % 8;                  // the first `more` XCDs take one more
+    for (int j = 0; j <= run; ++j)
       for (int q = 0; q < nsub; ++q)
-        for (int k = 0; k < 8; ++k) {
-          const int b = b0 + k * run + j;
-          if (b < nblk) out.push_back(make_int2(group, b * nsub + q));
-        }
+        for (int k = 0; k < 8; ++k)
+          if (j < run + (k < more ? 1 : 0)) out.push_back(make_int2(group, list[b0 + k * run + std::min(k, more) + j] * nsub + q));
+    b0 += n;
+  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -729,7 +743,7 @@ int Solver::rebuild() {
       if (mfma_slab)
         for (int b = 0; b < ops[o].nblk * ops[o].dev.nsub; ++b) ilh_nt[ilg[e].nt - 1].push_back(make_int2(e, b));
       else
-        xcd_runs(e, ops[o].nblk, ops[o].dev.nsub, ilh_nt[ilg[e].nt - 1]);
+        xcd_runs(ops[o].dev.g, e, ops[o].nblk, ops[o].dev.nsub, ilh_nt[ilg[e].nt - 1]);
     for (int b = 0; b < ops[o].nblk; ++b)
       for (int gi = 0; gi < ng; ++gi) hnon.push_back(make_int2(g0 + gi, b));
   }

@@ -1,6 +1,7 @@
-"""Host check (no GPU): the matrix-core stencil steps through a lattice by carries; site and
-neighbours at every position equal the brick order and the neighbours found from coordinates, for
-ranges that start anywhere in a brick and bricks smaller and larger than a wave's range."""
+"""Host check (no GPU): the matrix-core stencil steps through a lattice in pairs of sites by carries
+and keeps inputs from pair to pair; every site comes once and its neighbours are those found from
+coordinates, for ranges that start anywhere in a row, rows of one pair up, and bricks smaller and larger
+than a wave's range or of odd height."""
 import os
 import shutil
 import subprocess
@@ -26,7 +27,7 @@ def exe(tmp_path_factory):
 @pytest.mark.parametrize("dims", [(2, 2, 2, 2), (4, 2, 6, 4), (6, 4, 4, 10), (10, 6, 14, 6), (8, 8, 8, 16), (34, 4, 2, 6),
                                   (32, 8, 8, 8)])
 @pytest.mark.parametrize("brick", [(0, 0, 0), (1, 1, 1), (2, 1, 2)])
-def test_cursor_equals_brick_order(exe, dims, brick):
+def test_pair_cursor_finds_every_neighbour(exe, dims, brick):
     for nsub in (1, 4, 16):
         r = subprocess.run([exe, *map(str, dims), *map(str, brick), str(nsub)], capture_output=True, text=True)
         assert r.returncode == 0 and r.stdout.strip() == "ok", (nsub, r.stdout)
