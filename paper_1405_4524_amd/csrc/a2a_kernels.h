@@ -116,8 +116,9 @@ enum FinFrom {
   FIN_VEC_IL,    // the interleaved vector kernels: min(nsub, VEC_IL_SUB) per BS sites
 };
 constexpr int VEC_IL_SUB = 4;
-void launch_finalize(int kind, int from, const OpDev* ops, const SlotDev* slots, const int* list, int n, RedBuf rb,
-                     hipStream_t s);
+// most: an upper bound of the partials of a slot.
+void launch_finalize(int kind, int from, const OpDev* ops, const SlotDev* slots, const int* list, int n, int most,
+                     RedBuf rb, hipStream_t s);
 // Blocks per BS sites of the interleaved kernels, by the lattice alone (so that a source's result does
 // not depend on what shares its launches).
 int il_subblocks(int hv);

@@ -397,28 +397,45 @@ void launch_vec(int prec, const VecArgs& a, int ntiles, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------------------------
-// reduction finalize: one 64-thread block per slot, partials summed in block order
+// reduction finalize: one block per slot.  A slot with more than FIN_FEW partials takes all of the block's
+// 1024 threads, others one wave, whatever else is in the launch: a slot's sum does not depend on it.  (32^3x64
+// stencils, 8192 partials a slot: 49 us in a wave, @ in the block.)
 // ------------------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void k_finalize(int kind, int from, const OpDev* ops, const SlotDev* slots,
-                                                  const int* list, RedBuf rb) {
+constexpr int FIN_FEW = 512, FIN_THREADS = 1024;
+
+__global__ __launch_bounds__(FIN_THREADS) void k_finalize(int kind, int from, const OpDev* ops, const SlotDev* slots,
+                                                           const int* list, RedBuf rb) {
+  __shared__ double part[FIN_THREADS / 64][RED_NV];
   const int idx = list ? list[blockIdx.x] : (int)blockIdx.x;
   const SlotDev& sd = slots[idx];
   const double* p = rb.partials + (size_t)sd.sid * rb.maxblk * RED_NV;
   double v[RED_NV] = {0.0, 0.0, 0.0};
   const int nsub = ops[sd.op].nsub;
   const int nblk = sd.nblk * (!sd.il || from == FIN_SLOT ? 1 : from == FIN_MFMA ? nsub : min(nsub, VEC_IL_SUB));
-  for (int b = threadIdx.x; b < nblk; b += 64)
+  const int nth = nblk > FIN_FEW ? FIN_THREADS : 64;
+  if ((int)threadIdx.x < nth)
+    for (int b = threadIdx.x; b < nblk; b += nth)
 #pragma unroll
-    for (int k = 0; k < RED_NV; ++k) v[k] += p[(size_t)b * RED_NV + k];
+      for (int k = 0; k < RED_NV; ++k) v[k] += p[(size_t)b * RED_NV + k];
 #pragma unroll
   for (int k = 0; k < RED_NV; ++k) v[k] = wave_sum(v[k]);
+  if (nth > 64) {  // the same for the whole block
+    if (threadIdx.x % 64 == 0)
+#pragma unroll
+      for (int k = 0; k < RED_NV; ++k) part[threadIdx.x / 64][k] = v[k];
+    __syncthreads();
+    if (threadIdx.x == 0)
+      for (int w = 1; w < FIN_THREADS / 64; ++w)
+#pragma unroll
+        for (int k = 0; k < RED_NV; ++k) v[k] += part[w][k];
+  }
   if (threadIdx.x == 0) finalize_slot(kind, sd.scal, v, ops[sd.op].g.hv);
 }
 
-void launch_finalize(int kind, int from, const OpDev* ops, const SlotDev* slots, const int* list, int n, RedBuf rb,
-                     hipStream_t s) {
+void launch_finalize(int kind, int from, const OpDev* ops, const SlotDev* slots, const int* list, int n, int most,
+                     RedBuf rb, hipStream_t s) {
   if (n <= 0 || kind == RED_NONE) return;
-  hipLaunchKernelGGL(k_finalize, dim3(n), dim3(64), 0, s, kind, from, ops, slots, list, rb);
+  hipLaunchKernelGGL(k_finalize, dim3(n), dim3(most > FIN_FEW ? FIN_THREADS : 64), 0, s, kind, from, ops, slots, list, rb);
 }
 
 // ------------------------------------------------------------------------------------

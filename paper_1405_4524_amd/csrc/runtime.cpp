@@ -852,8 +852,10 @@ int Solver::upload_subset_vec(const std::vector<int>& idx) {
 }
 
 int Solver::finalize_red(bool sub, int kind, int from) {
-  launch_finalize(kind, from, d_ops, d_slots, sub ? d_sub_list : nullptr, sub ? sub_n : (int)live.size(), ctx->redbuf(),
-                  ctx->stream);
+  int most = 0;  // partials of a slot
+  for (const OpEntry& e : ops) most = std::max(most, prec >= 2 ? e.partials() : e.nblk);
+  launch_finalize(kind, from, d_ops, d_slots, sub ? d_sub_list : nullptr, sub ? sub_n : (int)live.size(), most,
+                  ctx->redbuf(), ctx->stream);
   A2A_HIP(ctx, hipGetLastError());
   return A2A_OK;
 }
