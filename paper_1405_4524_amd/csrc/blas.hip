@@ -399,7 +399,7 @@ void launch_vec(int prec, const VecArgs& a, int ntiles, hipStream_t s) {
 // ------------------------------------------------------------------------------------
 // reduction finalize: one block per slot.  A slot with more than FIN_FEW partials takes all of the block's
 // 1024 threads, others one wave, whatever else is in the launch: a slot's sum does not depend on it.  (32^3x64
-// stencils, 8192 partials a slot: 49 us in a wave, @ in the block.)
+// stencils, 8192 partials a slot: 49 us in a wave, 9 in the block.)
 // ------------------------------------------------------------------------------------
 constexpr int FIN_FEW = 512, FIN_THREADS = 1024;
 

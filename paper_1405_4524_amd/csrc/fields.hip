@@ -167,10 +167,13 @@ HD M3 m3_dag(const M3& a) {
 }
 
 HD long lex_shift(const Geo& g, const int c[4], int mu, int dm, int nu, int dn) {
-  int d[4] = {c[0], c[1], c[2], c[3]};
+  int d[4];
   const int L[4] = {g.X, g.Y, g.Z, g.T};
-  d[mu] = (d[mu] + dm + L[mu]) % L[mu];
-  d[nu] = (d[nu] + dn + L[nu]) % L[nu];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {  // no run-time index
+    const int v = c[k] + (k == mu ? dm : 0) + (k == nu ? dn : 0);
+    d[k] = v < 0 ? v + L[k] : v >= L[k] ? v - L[k] : v;
+  }
   return lex_index(g, d);
 }
 
@@ -226,61 +229,109 @@ HD void sigma_block(int plane, int b, int cf[3]) {
   for (int k = 0; k < 3; ++k) cf[k] = b ? dn[plane][k] : up[plane][k];
 }
 
-// packed G = i sum_{mu<nu} sigma_munu^(b) (x) F_munu for chiral block b at site c
-HD void clover_G_block(const Geo& g, const double* U, const int c[4], int b, double out[36]) {
-  // every loop unrolled: plane, sigma coefficients and matrix indices are compile-time
-  // constants (a run-time index into the coefficient tables would place them in scratch memory)
+// i F_munu is Hermitian, so F is nine reals: the three imaginary diagonal entries and the lower triangle
+struct F9 {
+  double v[9];
+  HD void put(const M3& f) {
+    v[0] = f.m[0].im;
+    v[1] = f.m[4].im;
+    v[2] = f.m[8].im;
+    v[3] = f.m[3].re;
+    v[4] = f.m[3].im;
+    v[5] = f.m[6].re;
+    v[6] = f.m[6].im;
+    v[7] = f.m[7].re;
+    v[8] = f.m[7].im;
+  }
+  HD M3 get() const {
+    M3 f;
+    f.m[0] = mk(0.0, v[0]);
+    f.m[4] = mk(0.0, v[1]);
+    f.m[8] = mk(0.0, v[2]);
+    f.m[3] = mk(v[3], v[4]);
+    f.m[1] = mk(-v[3], v[4]);
+    f.m[6] = mk(v[5], v[6]);
+    f.m[2] = mk(-v[5], v[6]);
+    f.m[7] = mk(v[7], v[8]);
+    f.m[5] = mk(-v[7], v[8]);
+    return f;
+  }
+};
+
+// packed G = i sum_{mu<nu} sigma_munu^(b) (x) F_munu for the chiral block b.  A block of six waves takes 64
+// sites: wave p the field strength of plane p (16 links, 12 products, one plane at a time in registers), then
+// two waves the two chiral blocks from LDS.  Bound by the link loads, 96 a site.  With one thread per site and
+// chiral block, every field strength was computed twice and the six planes of a thread waited for one another:
+// 32^3x64 7.5 ms, now 4.1; 12x10x6x14 64 us, now 29.
+constexpr int CF_SITES = 64;
+
+__global__ __launch_bounds__(6 * CF_SITES) void k_clover_field(Geo g, const double* U, double* G0, double* G1) {
+  __shared__ double sf[6][9][CF_SITES];
+  const int l = threadIdx.x % CF_SITES;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / CF_SITES);
+  const int site = blockIdx.x * CF_SITES + l, par = blockIdx.y;
+  if (site < g.hv) {
+    int c[4];
+    cb_coords(g, site, par, c);
+    // planes (01, 02, 03, 12, 13, 23)
+    const int mu = w < 3 ? 0 : w < 5 ? 1 : 2, nu = w < 3 ? w + 1 : w < 5 ? w - 1 : 3;
+    F9 f;
+    f.put(field_strength(g, U, c, mu, nu));
+#pragma unroll
+    for (int k = 0; k < 9; ++k) sf[w][k][l] = f.v[k];
+  }
+  __syncthreads();
+  if (w >= 2 || site >= g.hv) return;
+  // every loop unrolled: matrix indices are compile-time constants
   cx<double> G[36];
 #pragma unroll
   for (int k = 0; k < 36; ++k) G[k] = mk(0.0, 0.0);
 #pragma unroll
-  for (int mu = 0; mu < 4; ++mu)
+  for (int plane = 0; plane < 6; ++plane) {
+    F9 f9;
 #pragma unroll
-    for (int nu = mu + 1; nu < 4; ++nu) {
-      const int plane = mu == 0 ? nu - 1 : mu == 1 ? nu + 1 : 5;  // (01, 02, 03, 12, 13, 23)
-      M3 F = field_strength(g, U, c, mu, nu);
-      int cf[3];
-      sigma_block(plane, b, cf);
-      // M = c1 s1 + c2 s2 + c3 s3 = [[c3, c1 - i c2], [c1 + i c2, -c3]]
-      cx<double> M[4] = {mk((double)cf[2], 0.0), mk((double)cf[0], -(double)cf[1]),
-                         mk((double)cf[0], (double)cf[1]), mk(-(double)cf[2], 0.0)};
+    for (int k = 0; k < 9; ++k) f9.v[k] = sf[plane][k][l];
+    const M3 F = f9.get();
+    int up[3], dn[3], cf[3];
+    sigma_block(plane, 0, up);
+    sigma_block(plane, 1, dn);
 #pragma unroll
-      for (int s1 = 0; s1 < 2; ++s1)
+    for (int k = 0; k < 3; ++k) cf[k] = w ? dn[k] : up[k];
+    // M = c1 s1 + c2 s2 + c3 s3 = [[c3, c1 - i c2], [c1 + i c2, -c3]]
+    cx<double> M[4] = {mk((double)cf[2], 0.0), mk((double)cf[0], -(double)cf[1]), mk((double)cf[0], (double)cf[1]),
+                       mk(-(double)cf[2], 0.0)};
+    // entries that vanish in both chiral blocks
+    const bool diag = up[2] || dn[2], off = up[0] || up[1] || dn[0] || dn[1];
 #pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-          cx<double> im = mul_i(M[s1 * 2 + s2]);  // i M
-          if (im.re == 0.0 && im.im == 0.0) continue;
+    for (int s1 = 0; s1 < 2; ++s1)
 #pragma unroll
-          for (int a = 0; a < 3; ++a)
+      for (int s2 = 0; s2 < 2; ++s2) {
+        if (s1 == s2 ? !diag : !off) continue;
+        const cx<double> im = mul_i(M[s1 * 2 + s2]);  // i M
 #pragma unroll
-            for (int bb = 0; bb < 3; ++bb)
-              G[(s1 * 3 + a) * 6 + s2 * 3 + bb] = G[(s1 * 3 + a) * 6 + s2 * 3 + bb] + im * F.m[a * 3 + bb];
-        }
-    }
-  for (int i = 0; i < 6; ++i) out[i] = G[i * 6 + i].re;
-  for (int i = 1; i < 6; ++i)
-    for (int j = 0; j < i; ++j) {
-      out[tri_off(i, j)] = G[i * 6 + j].re;
-      out[tri_off(i, j) + 1] = G[i * 6 + j].im;
-    }
-}
-
-__global__ __launch_bounds__(BS) void k_clover_field(Geo g, const double* U, double* G0, double* G1) {
-  const int site = blockIdx.x * BS + threadIdx.x;
-  const int par = blockIdx.y;
-  const int b = blockIdx.z;
-  if (site >= g.hv) return;
-  int c[4];
-  cb_coords(g, site, par, c);
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+          for (int bb = 0; bb < 3; ++bb)
+            G[(s1 * 3 + a) * 6 + s2 * 3 + bb] = G[(s1 * 3 + a) * 6 + s2 * 3 + bb] + im * F.m[a * 3 + bb];
+      }
+  }
   double blk[36];
-  clover_G_block(g, U, c, b, blk);
+#pragma unroll
+  for (int i = 0; i < 6; ++i) blk[i] = G[i * 6 + i].re;
+#pragma unroll
+  for (int i = 1; i < 6; ++i)
+#pragma unroll
+    for (int j = 0; j < i; ++j) {
+      blk[tri_off(i, j)] = G[i * 6 + j].re;
+      blk[tri_off(i, j) + 1] = G[i * 6 + j].im;
+    }
   double* dst = (par ? G1 : G0);
-  CloverBlkF<double>::store<double>((char*)dst + b * CloverBlkF<double>::bytes(g.hv), g.hv, site, blk);
+  CloverBlkF<double>::store<double>((char*)dst + w * CloverBlkF<double>::bytes(g.hv), g.hv, site, blk);
 }
 
 void launch_clover_field(const Geo& g, const double* canon_links, double* G[2], hipStream_t s) {
-  dim3 grid((g.hv + BS - 1) / BS, 2, 2);
-  hipLaunchKernelGGL(k_clover_field, grid, dim3(BS), 0, s, g, canon_links, G[0], G[1]);
+  dim3 grid((g.hv + CF_SITES - 1) / CF_SITES, 2);
+  hipLaunchKernelGGL(k_clover_field, grid, dim3(6 * CF_SITES), 0, s, g, canon_links, G[0], G[1]);
 }
 
 // ------------------------------------------------------------------------------------
