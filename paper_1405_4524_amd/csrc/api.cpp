@@ -710,16 +710,7 @@ extern "C" int a2a_load_clover(a2a_ctx* h, int gauge_h, double csw, int* clover_
 }
 
 static void free_clover(Ctx* c, CloverField* cf) {
-  for (auto& k : cf->kops) {
-    for (int p = 0; p < 2; ++p) {
-      c->dfree(k->A64[p]);
-      c->dfree(k->Ai64[p]);
-      for (int q = 1; q < 4; ++q) {
-        c->dfree(k->Alo[q][p]);
-        c->dfree(k->Ailo[q][p]);
-      }
-    }
-  }
+  for (auto& k : cf->kops) free_kop(c, k.get());
   c->dfree(cf->G[0]);
   c->dfree(cf->G[1]);
 }

@@ -353,7 +353,7 @@ int Ctx::clover_full(KappaOp* k, int prec, long hv) {
   return A2A_OK;
 }
 
-static void free_kop(Ctx* c, KappaOp* k) {
+void free_kop(Ctx* c, KappaOp* k) {
   for (int p = 0; p < 2; ++p) {
     c->dfree(k->A64[p]);
     c->dfree(k->Ai64[p]);

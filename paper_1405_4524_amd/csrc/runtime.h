@@ -57,6 +57,8 @@ struct KappaOp {
   unsigned long long last_use = 0;
 };
 
+void free_kop(Ctx* c, KappaOp* k);  // every field of a kappa
+
 struct CloverField {
   int handle = 0;
   int gauge = 0;
