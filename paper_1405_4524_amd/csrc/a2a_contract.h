@@ -70,7 +70,10 @@ struct FillArgs {
   int dagger;                // store the spin-colour dagger of every 12 x 12 block
   double* partial;           // contract mode: [z][block] complex partials of sum C1 conj(C2)
 };
-long long fill_blocks(int M, int N);  // partials of a contraction, per z
+// most rows M of a fill, whose (M / 32)^2 one-wave blocks must be fewer than 2^32 threads, and of the
+// contractions (fill or Gram matrices), which launch the same for every larger M
+constexpr long long FILL_MAX_ROWS = (1LL << 18) - 1, FILL_CONTRACT_MAX_ROWS = 1LL << 21;
+int fill_blocks(int M, int N);  // blocks and partials of a contraction, per z
 void launch_fill(const FillArgs& a, int nz, hipStream_t s);
 void launch_fill_contract(const FillArgs& a, int nz, double* corr, hipStream_t s);
 void launch_pion_corr(int T, int n, const double* O, int mode, double* partial, double* corr, hipStream_t s);

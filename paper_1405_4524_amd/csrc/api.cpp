@@ -1350,12 +1350,12 @@ extern "C" int a2a_kernel_stats(a2a_ctx* h, const char* name, long long* launche
 // sum_{z,x} tr[S1 S2^dag]: through the filled propagators (the paper's method, cost ~ T (12
 // L^3)^2 N) and through Gram matrices of sources and solutions (cost ~ T 12 L^3 N^2)
 // =========================================================================================
-static int fill_geo(Ctx* c, const a2a_geom* geom, int nrhs, int t_src, Geo* g) {
+// max_rows: M = 12 X Y Z rows and columns of the fill that the entry point's launches hold
+static int fill_geo(Ctx* c, const a2a_geom* geom, int nrhs, int t_src, long long max_rows, Geo* g) {
   if (geom_to_geo(geom, g)) return c->fail(A2A_EINVAL, "bad lattice geometry");
   if (nrhs < 1) return c->fail(A2A_EINVAL, "nrhs must be positive");
   if (t_src < 0 || t_src >= g->T) return c->fail(A2A_EINVAL, "source timeslice out of range");
-  // M = 12 X Y Z rows and columns of the fill: (M / 32)^2 tiles must fit one launch
-  if (12LL * g->X * g->Y * g->Z > (1LL << 21)) return c->fail(A2A_EINVAL, "timeslice too large for the fill");
+  if (12LL * g->X * g->Y * g->Z > max_rows) return c->fail(A2A_EINVAL, "timeslice too large for the fill");
   return A2A_OK;
 }
 
@@ -1365,7 +1365,7 @@ extern "C" int a2a_fill_propagator_dev(a2a_ctx* h, const a2a_geom* geom, const d
   Ctx* c = &h->c;
   (void)hipSetDevice(c->device);
   Geo g;
-  A2A_TRY(fill_geo(c, geom, nrhs, t_src, &g));
+  A2A_TRY(fill_geo(c, geom, nrhs, t_src, FILL_MAX_ROWS, &g));
   if (t < 0 || t >= g.T) return c->fail(A2A_EINVAL, "sink timeslice out of range");
   const long long M = 12LL * g.X * g.Y * g.Z, col = M * g.T;  // complex per timeslice, per source
   FillArgs a{};
@@ -1390,7 +1390,7 @@ extern "C" int a2a_contract_fill_2pt_dev(a2a_ctx* h, const a2a_geom* geom, const
   Ctx* c = &h->c;
   (void)hipSetDevice(c->device);
   Geo g;
-  A2A_TRY(fill_geo(c, geom, nrhs, t_src, &g));
+  A2A_TRY(fill_geo(c, geom, nrhs, t_src, FILL_CONTRACT_MAX_ROWS, &g));
   const long long M = 12LL * g.X * g.Y * g.Z, col = M * g.T;
   FillArgs a{};
   a.P[0] = sol1;
@@ -1402,7 +1402,7 @@ extern "C" int a2a_contract_fill_2pt_dev(a2a_ctx* h, const a2a_geom* geom, const
   a.M = a.N = (int)M;
   a.K = nrhs;
   a.scale = 1.0 / nrhs;
-  const long long nb = fill_blocks(a.M, a.N);
+  const int nb = fill_blocks(a.M, a.N);
   void *part = nullptr, *dc = nullptr;
   A2A_TRY(c->dalloc(&part, sizeof(double) * 2 * (size_t)nb * g.T));
   int rc = c->dalloc(&dc, sizeof(double) * 2 * g.T);
@@ -1426,7 +1426,7 @@ extern "C" int a2a_contract_gram_2pt_dev(a2a_ctx* h, const a2a_geom* geom, const
   Ctx* c = &h->c;
   (void)hipSetDevice(c->device);
   Geo g;
-  A2A_TRY(fill_geo(c, geom, nrhs, t_src, &g));
+  A2A_TRY(fill_geo(c, geom, nrhs, t_src, FILL_CONTRACT_MAX_ROWS, &g));
   const int n = nrhs;
   const int ce = stoch_chunks(g, n, n, 1), cf = stoch_chunks(g, n, n, g.T);
   const size_t nn = (size_t)n * n;

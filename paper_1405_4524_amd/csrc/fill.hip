@@ -25,7 +25,8 @@
 //
 // Fill mode stores C, or the spin-colour dagger of its 12 x 12 blocks.  Contract mode multiplies two
 // products (S1 from the first operand pair, S2 from the second) tile by tile and accumulates sum C1 conj(C2)
-// without storing either: per-block FP64 partials, summed in block order by a second launch.
+// without storing either: a wave takes several tiles in turn, and a block's FP64 partial is summed in block
+// order by a second launch.
 #include "a2a_contract.h"
 #include "a2a_kernels.h"
 
@@ -35,10 +36,6 @@ namespace {
 
 typedef double d4v __attribute__((ext_vector_type(4)));
 typedef double d2v __attribute__((ext_vector_type(2)));
-// tiles along an edge in the contraction, whose two products hold twice the operands: 8^3x16 with 256
-// sources 42 ms (58 TFLOP/s), 47 with 2 x 2 tiles (operands move between register files), 62 before
-constexpr int FTC = 1;
-
 // global loads / stores through address-space-1 pointers (the arrays are device memory)
 __device__ __forceinline__ double2 ldc(const double* base, long long idx) {
   const d2v v = *(const __attribute__((address_space(1))) d2v*)(base + 2 * idx);
@@ -57,23 +54,11 @@ __device__ __forceinline__ d4v mfma(double a, double b, const d4v& c) {
 
 }  // namespace
 
-// MODE 0: store the product, 1: its spin-colour dagger, 2: contract two products; NT: 16-wide tiles along
-// an edge of the wave's tile
-template <int MODE, int NT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_fill(FillArgs a) {
-  constexpr int NP = MODE == 2 ? 2 : 1, E = 16 * NT;
-  const int lane = threadIdx.x, idx = lane & 15, kr = lane >> 4;
-  const int tiles_n = a.N / E;
-  const int m0 = (int)(blockIdx.x / tiles_n) * E, n0 = (int)(blockIdx.x % tiles_n) * E;
-  const long long z = blockIdx.y;
-  const double* P[NP];  // this lane's row and K offset
-  const double* Q[NP];
-#pragma unroll
-  for (int p = 0; p < NP; ++p) {
-    P[p] = a.P[p] + 2 * (z * a.pz + m0 + idx + kr * a.pk);
-    Q[p] = a.Q[p] + 2 * (z * a.qz + n0 + idx + kr * a.qk);
-  }
-  d4v cr[NP][NT][NT], ci[NP][NT][NT];
+// products of the operand pairs: NT x NT tiles of 16 x 16 each, from this lane's row and K offset
+template <int NP, int NT>
+__device__ __forceinline__ void fill_tile(const FillArgs& a, int kr, const double* const (&P)[NP],
+                                          const double* const (&Q)[NP], d4v (&cr)[NP][NT][NT],
+                                          d4v (&ci)[NP][NT][NT]) {
 #pragma unroll
   for (int p = 0; p < NP; ++p)
 #pragma unroll
@@ -85,7 +70,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
     double2 A[NP][NT], B[NP][NT];
   } s0, s1;
   auto load = [&](Step& s, int k0) {
-    long long k = k0;                                           // wave-uniform, but for the last step,
+    long long k = k0;                                  // wave-uniform, but for the last step,
     if (k0 + 4 > a.K) k = min(k0 + kr, a.K - 1) - kr;  // whose lanes past K read K - 1
 #pragma unroll
     for (int p = 0; p < NP; ++p)
@@ -131,9 +116,22 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
     load(s0, k0 + 8);
     step(s1, k0 + 4);
   }
+}
 
+// DAG: store the product's spin-colour dagger; NT: 16-wide tiles along an edge of the wave's tile
+template <bool DAG, int NT>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_fill(FillArgs a) {
+  constexpr int E = 16 * NT;
+  const int lane = threadIdx.x, idx = lane & 15, kr = lane >> 4;
+  const int tiles_n = a.N / E;
+  const int m0 = (int)(blockIdx.x / tiles_n) * E, n0 = (int)(blockIdx.x % tiles_n) * E;
+  const long long z = blockIdx.y;
+  const double* const P[1] = {a.P[0] + 2 * (z * a.pz + m0 + idx + kr * a.pk)};
+  const double* const Q[1] = {a.Q[0] + 2 * (z * a.qz + n0 + idx + kr * a.qk)};
+  d4v cr[1][NT][NT], ci[1][NT][NT];
+  fill_tile<1, NT>(a, kr, P, Q, cr, ci);
   // element q of a 16 x 16 accumulator tile is row 4 q + lane / 16, column lane % 16
-  if constexpr (MODE == 0) {
+  if constexpr (!DAG) {
 #pragma unroll
     for (int i = 0; i < NT; ++i)
 #pragma unroll
@@ -142,7 +140,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
         for (int q = 0; q < 4; ++q)
           stc(a.out + 2 * (z * a.oz + (m0 + 16 * i + 4 * q + kr) * a.om + n0 + 16 * j + idx),
               a.scale * cr[0][i][j][q], a.scale * ci[0][i][j][q]);
-  } else if constexpr (MODE == 1) {
+  } else {
     // (12 u + s, 12 v + s2) -> (12 u + s2, 12 v + s), conjugated
 #pragma unroll
     for (int i = 0; i < NT; ++i)
@@ -153,25 +151,46 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
           const int m = m0 + 16 * i + 4 * q + kr, n = n0 + 16 * j + idx, d = n % 12 - m % 12;
           stc(a.out + 2 * (z * a.oz + (m + d) * a.om + n - d), a.scale * cr[0][i][j][q], -a.scale * ci[0][i][j][q]);
         }
-  } else {
-    double vr = 0.0, vi = 0.0;
+  }
+}
+
+// sum C1 conj(C2) over 16 x 16 tiles (whose two products hold twice the operands of a stored one: 8^3x16 with
+// 256 sources 41.5 ms, 60 TFLOP/s; 2 x 2 tiles, where operands move between register files, took 12% longer).  A wave
+// takes every 4 gridDim.x-th tile in row-major order, so that the waves at work share rows and columns in the
+// L2s, and keeps its sum in registers.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_fill_contract(FillArgs a) {
+  const int lane = threadIdx.x & 63, idx = lane & 15, kr = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tm = a.M / 16, tn = a.N / 16, stride = 4 * (int)gridDim.x;
+  const long long z = blockIdx.y;
+  int row = (4 * (int)blockIdx.x + w) / tn, col = (4 * (int)blockIdx.x + w) % tn;
+  double v[2] = {0.0, 0.0};
+  while (row < tm) {
+    const double *P[2], *Q[2];
 #pragma unroll
-    for (int i = 0; i < NT; ++i)
+    for (int p = 0; p < 2; ++p) {
+      P[p] = a.P[p] + 2 * (z * a.pz + 16 * row + idx + kr * a.pk);
+      Q[p] = a.Q[p] + 2 * (z * a.qz + 16 * col + idx + kr * a.qk);
+    }
+    d4v cr[2][1][1], ci[2][1][1];
+    fill_tile<2, 1>(a, kr, P, Q, cr, ci);
 #pragma unroll
-      for (int j = 0; j < NT; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {  // C1 conj(C2)
-          const double r1 = cr[0][i][j][q], i1 = ci[0][i][j][q], r2 = cr[NP - 1][i][j][q], i2 = ci[NP - 1][i][j][q];
-          vr += r1 * r2 + i1 * i2;
-          vi += i1 * r2 - r1 * i2;
-        }
-    vr = wave_sum(vr * a.scale * a.scale);
-    vi = wave_sum(vi * a.scale * a.scale);
-    if (lane == 0) {
-      a.partial[2 * (z * gridDim.x + blockIdx.x)] = vr;
-      a.partial[2 * (z * gridDim.x + blockIdx.x) + 1] = vi;
+    for (int q = 0; q < 4; ++q) {
+      const double r1 = cr[0][0][0][q], i1 = ci[0][0][0][q], r2 = cr[1][0][0][q], i2 = ci[1][0][0][q];
+      v[0] += r1 * r2 + i1 * i2;
+      v[1] += i1 * r2 - r1 * i2;
+    }
+    row += stride / tn;
+    col += stride % tn;
+    if (col >= tn) {
+      col -= tn;
+      ++row;
     }
   }
+  v[0] *= a.scale * a.scale;
+  v[1] *= a.scale * a.scale;
+  block_sum_n<2, 256>(v);
+  if (threadIdx.x < 2) a.partial[2 * (z * gridDim.x + blockIdx.x) + threadIdx.x] = threadIdx.x == 0 ? v[0] : v[1];
 }
 
 // corr[z] = sum of the block partials of z, in block order
@@ -190,15 +209,22 @@ __global__ __launch_bounds__(64) void k_fill_sum(int nblk, const double* partial
   }
 }
 
-long long fill_blocks(int M, int N) { return (long long)(M / (16 * FTC)) * (N / (16 * FTC)); }
+// Blocks of four waves: one per 64 x 64 entries (four tiles a wave), up to 32 times the 512 that the chip
+// holds, from where on the waves take more tiles each instead.  With one wave and one partial per tile
+// 24^3x48 asked for 83 GB of partials and for more threads than a launch can have, and their sum was a good
+// part of the time: 16^3x2 with 8 sources 72.6 ms, now 12.6; 8^3x16 with 256 47.0, now 41.5; only the
+// smallest lose (2^3x4 with 64 27 us, now 39, three tiles in turn).
+int fill_blocks(int M, int N) {
+  return (int)std::min(16384LL, (long long)((M + 63) / 64) * ((N + 63) / 64));
+}
 
 template <int NT>
 static void launch_fill_t(const FillArgs& a, int nz, hipStream_t s) {
   const dim3 g((unsigned)((long long)(a.M / (16 * NT)) * (a.N / (16 * NT))), (unsigned)nz);
   if (a.dagger)
-    hipLaunchKernelGGL((k_fill<1, NT>), g, dim3(64), 0, s, a);
+    hipLaunchKernelGGL((k_fill<true, NT>), g, dim3(64), 0, s, a);
   else
-    hipLaunchKernelGGL((k_fill<0, NT>), g, dim3(64), 0, s, a);
+    hipLaunchKernelGGL((k_fill<false, NT>), g, dim3(64), 0, s, a);
 }
 
 // 2 x 2 tiles from 1024 rows on; below, four times the waves fill more of the chip (768 rows, 128 sources: 36
@@ -211,8 +237,8 @@ void launch_fill(const FillArgs& a, int nz, hipStream_t s) {
 }
 
 void launch_fill_contract(const FillArgs& a, int nz, double* corr, hipStream_t s) {
-  const int nb = (int)fill_blocks(a.M, a.N);
-  hipLaunchKernelGGL((k_fill<2, FTC>), dim3((unsigned)nb, (unsigned)nz), dim3(64), 0, s, a);
+  const int nb = fill_blocks(a.M, a.N);
+  hipLaunchKernelGGL(k_fill_contract, dim3((unsigned)nb, (unsigned)nz), dim3(256), 0, s, a);
   hipLaunchKernelGGL(k_fill_sum, dim3((unsigned)nz), dim3(64), 0, s, nb, a.partial, corr);
 }
 
