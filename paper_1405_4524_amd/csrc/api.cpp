@@ -112,13 +112,11 @@ int il_alloc(Ctx* c, Slot* slots, int n, long hv, int nlo, int width) {
 
 // arenas of n slots of one operator: per slot, or interleaved groups for FP16 / BF16.  Whole
 // 16-lane tiles go to interleaved groups; a remainder of at least IL_REM_MIN sources gets a
-// tile of its own, a smaller one stays per slot: a tile costs the same whatever its fill, and the
-// per-thread stencil is cheaper per RHS below that (32^3x64: 1550 us for a tile, 1880 for 12 per-thread
-// sources; 16^3x32: 89 us for one more tile, 117 for 12).  Beside whole tiles on a lattice where
-// launches cost more than the work (IL_REM_HV), any remainder joins them (8^3x16, 16 + 4 sources: the
-// second tile adds 3 us to the pair, four per-slot sources 19 us and their own vector launches).
-constexpr int IL_REM_MIN = 9;
-constexpr long IL_REM_HV = 1L << 15;
+// tile of its own, a smaller one stays per slot.  The line is one of precision as well as of time: the
+// matrix cores round the hopping term to the storage format before A^-1 and sum a wave's dot products in
+// FP32, the per-thread stencil holds the one in FP32 and the others in FP64.  (A tile costs the same whatever
+// its fill, 32^3x64 1550 us for the Schur pair where 12 per-thread sources take 1880.)
+constexpr int IL_REM_MIN = 12;
 
 // ilw: RHS per interleaved group (16, 32 or 48; 0 = the context's option)
 int slots_alloc(Ctx* c, Slot* slots, int n, int prec, long hv, int nblk, int nlo, int nhi, int ilw = 0) {
@@ -128,7 +126,7 @@ int slots_alloc(Ctx* c, Slot* slots, int n, int prec, long hv, int nblk, int nlo
   int n_il = 0;
   if (il) {
     n_il = n / 16 * 16;
-    if (n - n_il >= IL_REM_MIN || (n_il > 0 && hv <= IL_REM_HV)) n_il = n;
+    if (n - n_il >= IL_REM_MIN) n_il = n;
   }
   int rc = A2A_OK;
   int k = 0;
