@@ -318,7 +318,9 @@ int a2a_dilute_dev(a2a_ctx *ctx, const a2a_geom *geom, const double *noise_dev, 
  * a2a_dilute_dev with this scheme (nrhs = n D; sources a and b belong to noise vectors a / D
  * and b / D), normalised by 1 / (T n (n - 1)) (mode 0), or over all pairs without
  * normalisation (mode 3, e.g. for full dilution).  With time dilution (A2A_DILUTE_T, _TSC)
- * only the pieces on timeslice t enter O(t), which cuts the work by T.  corr: host complex
+ * only the pieces on timeslice t enter O(t), which cuts the work by T.  With spin-colour dilution
+ * (A2A_DILUTE_SC, _TSC) the sums run over each piece's own component, a twelfth of the work; sources
+ * with other entries that are not zero are found out and summed over in full.  corr: host complex
  * [nmom][T].  With A2A_DILUTE_NONE, p = 0 and mode 0 this is a2a_contract_pion_2pt's
  * unbiased correlator. */
 int a2a_contract_pion_mom_dev(a2a_ctx *ctx, const a2a_geom *geom, const double *sources_dev,

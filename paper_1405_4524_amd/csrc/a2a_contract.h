@@ -30,8 +30,16 @@ struct MomPairs {
   int nm;
   int ip[MOM_BATCH], im[MOM_BATCH];
 };
+// Support of spin-colour diluted sources: off [SC_CHECK_BLOCKS] is not zero where one has entries other than
+// zero outside its own component (off null: not asked for)
+constexpr int SC_CHECK_BLOCKS = 1024;
+struct ScCheck {
+  const double* eta;
+  int nv, group, time;
+  int* off;
+};
 // f: complex [nph][V3]
-void launch_phases(const Geo& g, const MomBatch& m, double* f, hipStream_t s);
+void launch_phases(const Geo& g, const MomBatch& m, double* f, const ScCheck& check, hipStream_t s);
 // operators O [T][nph][12 nv][n] of spin-colour diluted sources (row 12 i + c: noise vector i, component
 // c; source i group + c, plus 12 t if time is set); partial: nchunk times that (not used for one chunk)
 int stoch_sc_chunks(const Geo& g, int nv, int nph, int n);

@@ -1588,7 +1588,9 @@ extern "C" int a2a_contract_pion_mom_dev(a2a_ctx* h, const a2a_geom* geom, const
         for (int q = 0; q < per_t; ++q) rows[(size_t)t * na + i * per_t + q] = i * group + per_t * t + q;
   }
   const size_t nn = (size_t)na * n, V3 = (size_t)g.X * g.Y * g.Z;
-  const bool by_sc = scheme == A2A_DILUTE_SC || scheme == A2A_DILUTE_TSC;
+  // spin-colour pieces take the products over their own component; a call whose first batch finds entries
+  // outside it takes the full products instead (the check's answer comes with the batch's results)
+  bool by_sc = scheme == A2A_DILUTE_SC || scheme == A2A_DILUTE_TSC, check = by_sc;
   // momenta in batches whose operators (and their chunk sums) stay below MOM_BATCH_BYTES, at least one
   constexpr double MOM_BATCH_BYTES = 1e9;
   Scratch rowmem(c);
@@ -1622,14 +1624,16 @@ extern "C" int a2a_contract_pion_mom_dev(a2a_ctx* h, const a2a_geom* geom, const
     if (!rc && nchunk > 1) rc = mem.get(&part, nO * nchunk);
     if (!rc) rc = mem.get(&ph, 2 * V3 * mb.nph);
     if (!rc) rc = mem.get(&pairs, 2 * (by_time ? (size_t)mp.nm * g.T * g.T : pair_corr_partials(g.T, n, mp.nm)));
-    if (!rc) rc = mem.get(&dc, 2 * (size_t)mp.nm * g.T);
+    const size_t ncorr = 2 * (size_t)mp.nm * g.T, noff = check ? SC_CHECK_BLOCKS / 2 : 0;  // doubles
+    if (!rc) rc = mem.get(&dc, ncorr + noff);
     if (rc == A2A_ENOMEM && mp.nm > 1) {  // a batch that does not fit: one momentum at a time
       c->err.clear();
       most = 1;
       continue;
     }
     if (rc) return rc;
-    launch_phases(g, mb, ph, c->stream);
+    const ScCheck sc{src, nv, group, by_time, check ? (int*)(dc + ncorr) : nullptr};
+    launch_phases(g, mb, ph, sc, c->stream);
     if (by_sc)
       launch_stoch_sc(g, n, nv, mb.nph, group, by_time, src, sol, ph, part, nchunk, O, c->stream);
     else
@@ -1640,7 +1644,17 @@ extern "C" int a2a_contract_pion_mom_dev(a2a_ctx* h, const a2a_geom* geom, const
       launch_pion_mom(g.T, n, mb.nph, group, mode, mp, O, pairs, dc, c->stream);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return c->fail(A2A_EDEVICE, std::string("momentum contraction: ") + hipGetErrorString(e));
-    A2A_TRY(copy_to_host(c, corr + 2 * (size_t)m0 * g.T, dc, sizeof(double) * 2 * mp.nm * g.T));
+    std::vector<double> res(ncorr + noff);
+    A2A_TRY(copy_to_host(c, res.data(), dc, sizeof(double) * res.size()));
+    if (check) {
+      check = false;
+      const int* off = (const int*)(res.data() + ncorr);
+      if (std::any_of(off, off + SC_CHECK_BLOCKS, [](int v) { return v != 0; })) {
+        by_sc = false;
+        continue;
+      }
+    }
+    std::memcpy(corr + 2 * (size_t)m0 * g.T, res.data(), sizeof(double) * ncorr);
     m0 += mp.nm;
   }
   return A2A_OK;

@@ -382,9 +382,37 @@ void launch_pipi_mixed(int T, int t0, int n1, int n2, const double* Pn, const do
 // ------------------------------------------------------------------------------------
 // momentum phases and spin-colour diluted operators
 // ------------------------------------------------------------------------------------
-// f[k][y] = exp(-i p_k.y) on the spatial sites of a timeslice (x fastest), the angle reduced exactly
-__global__ __launch_bounds__(256) void k_phases(int X, int Y, int V3, MomBatch m, double* f) {
-  const int s = blockIdx.x * 256 + threadIdx.x, k = blockIdx.y;
+// off[block] = 1 if the block met an element outside its source's own component that is not zero: of source
+// (i, c) over the whole lattice, or with time over the piece's own timeslice.
+constexpr int SC_CHECK_SPAN = 1024;  // elements a block takes at a time
+
+__device__ void sc_check_block(const ScCheck& k, int block, int T, int V3) {
+  const long V = (long)V3 * T, len = 12L * (k.time ? V3 : V), spans = (len + SC_CHECK_SPAN - 1) / SC_CHECK_SPAN;
+  const int runs = 12 * k.nv * (k.time ? T : 1);
+  int bad = 0;
+  for (long u = block; u < runs * spans; u += SC_CHECK_BLOCKS) {
+    const int run = (int)(u / spans), c = run % 12, t = k.time ? run / 12 % T : 0, i = run / (k.time ? 12 * T : 12);
+    const long e0 = u % spans * SC_CHECK_SPAN;
+    const double2* p = (const double2*)k.eta + ((size_t)i * k.group + 12 * t + c) * 12 * V + (size_t)t * 12 * V3 + e0;
+    const int r0 = (int)(e0 % 12), left = (int)min((long)SC_CHECK_SPAN, len - e0);
+#pragma unroll
+    for (int q = 0; q < SC_CHECK_SPAN / 256; ++q) {
+      const int e = 256 * q + threadIdx.x;
+      const double2 v = p[min(e, left - 1)];
+      bad |= e < left && (r0 + e) % 12 != c && !(v.x == 0.0 && v.y == 0.0);
+    }
+  }
+  bad = __syncthreads_or(bad);
+  if (threadIdx.x == 0) k.off[block] = bad != 0;
+}
+
+// f[k][y] = exp(-i p_k.y) on the spatial sites of a timeslice (x fastest), the angle reduced exactly; the
+// blocks after those check the sources' support (at the memory rate: 75 MB for 8^3x16 with 768
+// time-spin-colour pieces, 15 us of 760; a launch of its own would cost short calls as much again)
+__global__ __launch_bounds__(256) void k_phases(int X, int Y, int V3, int T, MomBatch m, double* f, ScCheck check) {
+  const int per = (V3 + 255) / 256, b = blockIdx.x;
+  if (b >= per * m.nph) return sc_check_block(check, b - per * m.nph, T, V3);
+  const int s = b % per * 256 + threadIdx.x, k = b / per;
   if (s >= V3) return;
   const int x = s % X, y = s / X % Y, z = s / (X * Y), Z = V3 / (X * Y);
   const long long* p = m.p[k];
@@ -394,9 +422,9 @@ __global__ __launch_bounds__(256) void k_phases(int X, int Y, int V3, MomBatch m
   ((double2*)f)[(size_t)k * V3 + s] = make_double2(cs, -sn);
 }
 
-void launch_phases(const Geo& g, const MomBatch& m, double* f, hipStream_t s) {
-  const int V3 = g.X * g.Y * g.Z;
-  hipLaunchKernelGGL(k_phases, dim3((unsigned)((V3 + 255) / 256), (unsigned)m.nph), dim3(256), 0, s, g.X, g.Y, V3, m, f);
+void launch_phases(const Geo& g, const MomBatch& m, double* f, const ScCheck& check, hipStream_t s) {
+  const int V3 = g.X * g.Y * g.Z, blocks = (V3 + 255) / 256 * m.nph + (check.off ? SC_CHECK_BLOCKS : 0);
+  hipLaunchKernelGGL(k_phases, dim3((unsigned)blocks), dim3(256), 0, s, g.X, g.Y, V3, g.T, m, f, check);
 }
 
 // Stochastic operators of spin-colour diluted sources (schemes SC and TSC): the source (i, c) is zero
