@@ -611,11 +611,13 @@ __global__ __launch_bounds__(256) void k_pair_corr(int T, int n, int nph, int gr
     }
     for (int k = threadIdx.x; k < DT * E; k += 256) {
       const int r = k / E, e = k % E, b = b0 + e / EB, a = a0 + e % EB;  // consecutive a: O[b][a] in runs
-      ys[r][(e % EB) * EB + e / EB] =
-          t0 + r < T && a < n && b < n ? Oc[(((size_t)(t0 + r) * nph + im) * n + b) * n + a] : make_double2(0.0, 0.0);
+      const bool on = t0 + r < T && a < n && b < n && !(skip && a / group == b / group);
+      ys[r][(e % EB) * EB + e / EB] = on ? Oc[(((size_t)(t0 + r) * nph + im) * n + b) * n + a] : make_double2(0.0, 0.0);
     }
     __syncthreads();
-    for (int k = 0; k < PER; ++k) {
+    // a dropped pair or timeslice must not meet the other factor, which may be infinite: both factors of a
+    // pair are zero, and rows past T are left out
+    for (int k = 0; k < PER && t0 + part * PER + k < T; ++k) {
       const int r = part * PER + k;
 #pragma unroll 8
       for (int e = 0; e < E; ++e) {
