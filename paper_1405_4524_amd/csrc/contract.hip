@@ -597,36 +597,39 @@ __global__ __launch_bounds__(256) void k_pair_corr(int T, int n, int nph, int gr
   constexpr int E = EB * EB, PARTS = 256 / DT, PER = DT / PARTS;  // PER t0 per part and tile of DT
   __shared__ double2 xs[2 * DT - 1][E + 1], ys[DT][E + 1];
   const int nb = (n + EB - 1) / EB;
-  const int a0 = blockIdx.x / nb * EB, b0 = blockIdx.x % nb * EB, d0 = blockIdx.y * DT, m = blockIdx.z;
+  const int d0 = blockIdx.y * DT, m = blockIdx.z;
   const int ip = mp.ip[m], im = mp.im[m];
   const double2* Oc = (const double2*)O;
   const int dt = threadIdx.x % DT, part = threadIdx.x / DT;
   double vr = 0.0, vi = 0.0;
-  for (int t0 = 0; t0 < T; t0 += DT) {
-    for (int k = threadIdx.x; k < (2 * DT - 1) * E; k += 256) {  // rows t0 + d0 + 0 .. 2 DT - 2 (mod T)
-      const int r = k / E, e = k % E, a = a0 + e / EB, b = b0 + e % EB;
-      const bool on = a < n && b < n && !(skip && a / group == b / group);
-      const int t1 = (t0 + d0 + r) % T;
-      xs[r][e] = on ? Oc[(((size_t)t1 * nph + ip) * n + a) * n + b] : make_double2(0.0, 0.0);
-    }
-    for (int k = threadIdx.x; k < DT * E; k += 256) {
-      const int r = k / E, e = k % E, b = b0 + e / EB, a = a0 + e % EB;  // consecutive a: O[b][a] in runs
-      const bool on = t0 + r < T && a < n && b < n && !(skip && a / group == b / group);
-      ys[r][(e % EB) * EB + e / EB] = on ? Oc[(((size_t)(t0 + r) * nph + im) * n + b) * n + a] : make_double2(0.0, 0.0);
-    }
-    __syncthreads();
-    // a dropped pair or timeslice must not meet the other factor, which may be infinite: both factors of a
-    // pair are zero, and rows past T are left out
-    for (int k = 0; k < PER && t0 + part * PER + k < T; ++k) {
-      const int r = part * PER + k;
-#pragma unroll 8
-      for (int e = 0; e < E; ++e) {
-        const double2 x = xs[r + dt][e], y = ys[r][e];
-        vr += x.x * y.x - x.y * y.y;
-        vi += x.x * y.y + x.y * y.x;
+  for (int u = blockIdx.x; u < nb * nb; u += gridDim.x) {  // the block's patches
+    const int a0 = u / nb * EB, b0 = u % nb * EB;
+    for (int t0 = 0; t0 < T; t0 += DT) {
+      for (int k = threadIdx.x; k < (2 * DT - 1) * E; k += 256) {  // rows t0 + d0 + 0 .. 2 DT - 2 (mod T)
+        const int r = k / E, e = k % E, a = a0 + e / EB, b = b0 + e % EB;
+        const bool on = a < n && b < n && !(skip && a / group == b / group);
+        const int t1 = (t0 + d0 + r) % T;
+        xs[r][e] = on ? Oc[(((size_t)t1 * nph + ip) * n + a) * n + b] : make_double2(0.0, 0.0);
       }
+      for (int k = threadIdx.x; k < DT * E; k += 256) {
+        const int r = k / E, e = k % E, b = b0 + e / EB, a = a0 + e % EB;  // consecutive a: O[b][a] in runs
+        const bool on = t0 + r < T && a < n && b < n && !(skip && a / group == b / group);
+        ys[r][(e % EB) * EB + e / EB] = on ? Oc[(((size_t)(t0 + r) * nph + im) * n + b) * n + a] : make_double2(0.0, 0.0);
+      }
+      __syncthreads();
+      // a dropped pair or timeslice must not meet the other factor, which may be infinite: both factors of a
+      // pair are zero, and rows past T are left out
+      for (int k = 0; k < PER && t0 + part * PER + k < T; ++k) {
+        const int r = part * PER + k;
+#pragma unroll 8
+        for (int e = 0; e < E; ++e) {
+          const double2 x = xs[r + dt][e], y = ys[r][e];
+          vr += x.x * y.x - x.y * y.y;
+          vi += x.x * y.y + x.y * y.x;
+        }
+      }
+      __syncthreads();
     }
-    __syncthreads();
   }
   double2* red = &xs[0][0];  // [PARTS][DT]
   red[part * DT + dt] = make_double2(vr, vi);
@@ -675,21 +678,24 @@ __global__ __launch_bounds__(256) void k_pair_corr_rows(int T, int N, int na, in
 
 // few timeslices: 16 separations x 16 parts on 8 x 8 patches; else 64 x 4 on 4 x 4
 static int pair_edge(int T) { return T <= 16 ? 8 : 4; }
-size_t pair_corr_partials(int T, int n, int nm) {
-  const size_t nb = (n + pair_edge(T) - 1) / pair_edge(T);
-  return (size_t)nm * T * nb * nb;
+// Blocks: one per patch, up to many times what the chip holds, from where on they take more patches (one
+// each would be more threads than a launch can have from 32768 sources on, 16384 with many timeslices)
+static int pair_blocks(int T, int n) {
+  const int nb = (n + pair_edge(T) - 1) / pair_edge(T);
+  return std::min(nb * nb, 1 << 16);
 }
+size_t pair_corr_partials(int T, int n, int nm) { return (size_t)nm * T * pair_blocks(T, n); }
 
 static void launch_pair_corr(int T, int n, int nph, int group, int skip, const MomPairs& mp, double norm, const double* O,
                              double* partial, double* corr, hipStream_t s) {
-  const int eb = pair_edge(T), nb = (n + eb - 1) / eb;
+  const int nblk = pair_blocks(T, n);
   if (T <= 16)
-    hipLaunchKernelGGL((k_pair_corr<16, 8>), dim3((unsigned)(nb * nb), 1, mp.nm), dim3(256), 0, s, T, n, nph, group, skip,
-                       mp, O, partial);
+    hipLaunchKernelGGL((k_pair_corr<16, 8>), dim3((unsigned)nblk, 1, mp.nm), dim3(256), 0, s, T, n, nph, group, skip, mp,
+                       O, partial);
   else
-    hipLaunchKernelGGL((k_pair_corr<64, 4>), dim3((unsigned)(nb * nb), (unsigned)((T + 63) / 64), mp.nm), dim3(256), 0, s, T,
-                       n, nph, group, skip, mp, O, partial);
-  hipLaunchKernelGGL(k_corr_sum, dim3((unsigned)(mp.nm * T)), dim3(256), 0, s, nb * nb, norm, partial, corr);
+    hipLaunchKernelGGL((k_pair_corr<64, 4>), dim3((unsigned)nblk, (unsigned)((T + 63) / 64), mp.nm), dim3(256), 0, s, T, n,
+                       nph, group, skip, mp, O, partial);
+  hipLaunchKernelGGL(k_corr_sum, dim3((unsigned)(mp.nm * T)), dim3(256), 0, s, nblk, norm, partial, corr);
 }
 
 // Momentum-projected pions over pairs of sources from different noise vectors, normalised by
