@@ -405,12 +405,28 @@ int fields_on_device(Ctx* c, Scratch& mem, bool dev, size_t nel, const double** 
   return A2A_OK;
 }
 
-// O [T][n][n] into O_dev
-int contract_ops(Ctx* c, Scratch& mem, const Geo& g, const double* src, const double* sol, int n, double* O_dev) {
-  const int nchunk = stoch_chunks(g, n, n, g.T);
-  double* part = nullptr;
-  if (nchunk > 1) A2A_TRY(mem.get(&part, 2 * (size_t)g.T * nchunk * n * n));
-  launch_stoch_ops(g, n, src, sol, part, nchunk, O_dev, c->stream);
+// Partial sums of nchunk chunks (per doubles each): fewer chunks where the memory budget does not hold
+// them, and none for a single one, which needs no sum.  Taken after the buffers a call cannot do without.
+int chunks_that_fit(Ctx* c, Scratch& mem, size_t per, int* nchunk, double** part) {
+  *part = nullptr;
+  for (; *nchunk > 1; *nchunk /= 2) {
+    const int rc = mem.get(part, per * *nchunk);
+    if (rc != A2A_ENOMEM) return rc;
+    c->err.clear();
+  }
+  return A2A_OK;
+}
+
+// launch_stoch_ops with partial sums of its own (their buffer is free for the next launch of the stream)
+int stoch_ops(Ctx* c, const Geo& g, int n, const double* eta, const double* X, double* O, int g5 = 1, int t_first = 0,
+              int nt = -1, const double* phase = nullptr, const int* rows = nullptr, int na = 0, int ns = 0) {
+  if (nt < 0) nt = g.T;
+  if (na <= 0) na = n;
+  Scratch mem(c);
+  int nchunk = stoch_chunks(g, na, n, nt);
+  double* part;
+  A2A_TRY(chunks_that_fit(c, mem, 2 * (size_t)nt * na * n, &nchunk, &part));
+  launch_stoch_ops(g, n, eta, X, part, nchunk, O, c->stream, g5, t_first, nt, phase, rows, na, ns);
   A2A_HIP(c, hipGetLastError());
   return A2A_OK;
 }
@@ -1204,7 +1220,7 @@ static int pion_impl(a2a_ctx* h, const a2a_geom* geom, const double* src, const 
   A2A_TRY(mem.get(&out, 2 * g.T + nO));
   A2A_TRY(mem.get(&pairs, 2 * pair_corr_partials(g.T, n, 1)));
   double* O = out + 2 * g.T;
-  A2A_TRY(contract_ops(c, mem, g, src, sol, n, O));
+  A2A_TRY(stoch_ops(c, g, n, src, sol, O));
   launch_pion_corr(g.T, n, O, mode, pairs, out, c->stream);
   A2A_HIP(c, hipGetLastError());
   const size_t both = 2 * g.T + nO;
@@ -1275,7 +1291,7 @@ static int pipi_impl(a2a_ctx* h, const a2a_geom* geom, const double* src, const 
   A2A_TRY(mem.get(&work, 2 * pipi_work(g.T, n)));
   A2A_TRY(mem.get(&out, 2 * 6 * (size_t)g.T));
   if (pion) A2A_TRY(mem.get(&pairs, 2 * pair_corr_partials(g.T, n, 1)));
-  A2A_TRY(contract_ops(c, mem, g, src, sol, n, O));
+  A2A_TRY(stoch_ops(c, g, n, src, sol, O));
   launch_pipi(g.T, n, O, work, out, out + 8 * g.T, c->stream);
   if (pion) launch_pion_corr(g.T, n, O, A2A_PION_UNBIASED, pairs, out + 10 * g.T, c->stream);
   A2A_HIP(c, hipGetLastError());
@@ -1426,28 +1442,18 @@ extern "C" int a2a_contract_gram_2pt_dev(a2a_ctx* h, const a2a_geom* geom, const
   Geo g;
   A2A_TRY(fill_geo(c, geom, nrhs, t_src, FILL_CONTRACT_MAX_ROWS, &g));
   const int n = nrhs;
-  const int ce = stoch_chunks(g, n, n, 1), cf = stoch_chunks(g, n, n, g.T);
   const size_t nn = (size_t)n * n;
-  void *part = nullptr, *E = nullptr, *F = nullptr, *dc = nullptr;
-  A2A_TRY(c->dalloc(&part, sizeof(double) * 2 * std::max((size_t)ce, (size_t)g.T * cf) * nn));
-  int rc = c->dalloc(&E, sizeof(double) * 2 * nn);
-  if (!rc) rc = c->dalloc(&F, sizeof(double) * 2 * nn * g.T);
-  if (!rc) rc = c->dalloc(&dc, sizeof(double) * 2 * g.T);
-  if (!rc) {
-    // E[i][j] = <eta1_i, eta2_j> on t_src; F[t][j][i] = <X2_j, X1_i> on t
-    launch_stoch_ops(g, n, src1, src2, (double*)part, ce, (double*)E, c->stream, 0, t_src, 1);
-    launch_stoch_ops(g, n, sol2, sol1, (double*)part, cf, (double*)F, c->stream, 0, 0, g.T);
-    launch_gram_corr(g.T, n, (const double*)E, (const double*)F, (double*)dc, c->stream);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) rc = c->fail(A2A_EDEVICE, std::string("Gram contraction: ") + hipGetErrorString(e));
-    if (!rc) rc = copy_to_host(c, corr, dc, sizeof(double) * 2 * g.T);
-  }
-  c->sync();
-  c->dfree(part);
-  c->dfree(E);
-  c->dfree(F);
-  c->dfree(dc);
-  return rc;
+  Scratch mem(c);
+  double *E, *F, *dc;
+  A2A_TRY(mem.get(&E, 2 * nn));
+  A2A_TRY(mem.get(&F, 2 * nn * g.T));
+  A2A_TRY(mem.get(&dc, 2 * (size_t)g.T));
+  // E[i][j] = <eta1_i, eta2_j> on t_src; F[t][j][i] = <X2_j, X1_i> on t
+  A2A_TRY(stoch_ops(c, g, n, src1, src2, E, 0, t_src, 1));
+  A2A_TRY(stoch_ops(c, g, n, sol2, sol1, F, 0));
+  launch_gram_corr(g.T, n, E, F, dc, c->stream);
+  A2A_HIP(c, hipGetLastError());
+  return copy_to_host(c, corr, dc, sizeof(double) * 2 * g.T);
 }
 
 // =========================================================================================
@@ -1484,48 +1490,25 @@ extern "C" int a2a_contract_pipi_mixed_dev(a2a_ctx* h, const a2a_geom* geom, con
     const double* a;
     int na;
     const double* b;
-    int nb, t_first, nt, nchunk;
-    size_t elems;  // complex outputs
+    int nb, t_first, nt;
   };
-  Gram gm[5] = {{point_sol, 12, point_sol, 12, 0, T, 0, 0},  // Pn[t][k][l] = <Sp_k, Sp_l>_t
-                {src1, n1, src2, n2, 0, T, 0, 0},             // G[t][i][j] = <eta1_i, eta2_j>_t
-                {sol1, n1, sol2, n2, 0, T, 0, 0},             // Fp[t][i][j] = <X1_i, X2_j>_t
-                {point_sol, 12, sol1, n1, t0, 1, 0, 0},       // A[k][i] = <Sp_k, X1_i>_t0
-                {sol2, n2, point_sol, 12, 0, T, 0, 0}};       // B[t][j][k] = <X2_j, Sp_k>_t
-  size_t part_elems = 0;
-  for (Gram& q : gm) {
-    q.nchunk = stoch_chunks(g, q.na, q.nb, q.nt);
-    q.elems = (size_t)q.nt * q.na * q.nb;
-    part_elems = std::max(part_elems, q.elems * q.nchunk);
-  }
-  const int nmix = pipi_mixed_chunks(n1);
-  void* part = nullptr;
-  void* out[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
-  void *mix = nullptr, *dd = nullptr;
-  A2A_TRY(c->dalloc(&part, sizeof(double) * 2 * part_elems));
-  int rc = A2A_OK;
-  for (int q = 0; q < 5 && !rc; ++q) rc = c->dalloc(&out[q], sizeof(double) * 2 * gm[q].elems);
-  if (!rc) rc = c->dalloc(&mix, sizeof(double) * 6 * (size_t)T * nmix);
-  if (!rc) rc = c->dalloc(&dd, sizeof(double) * 2 * 7 * (size_t)T);  // diagrams [4][T], pieces [3][T]
-  if (!rc) {
-    // one partial buffer: every Gram launch pair finishes before the next starts (one stream)
-    for (int q = 0; q < 5; ++q)
-      launch_stoch_ops(g, gm[q].nb, gm[q].a, gm[q].b, (double*)part, gm[q].nchunk, (double*)out[q], c->stream, 0,
-                       gm[q].t_first, gm[q].nt, nullptr, nullptr, gm[q].na);
-    double* d = (double*)dd;
-    launch_pipi_mixed(T, t0, n1, n2, (const double*)out[0], (const double*)out[1], (const double*)out[2],
-                      (const double*)out[3], (const double*)out[4], (double*)mix, d, d + 8 * T, c->stream);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) rc = c->fail(A2A_EDEVICE, std::string("mixed pi-pi contraction: ") + hipGetErrorString(e));
-    if (!rc) rc = copy_to_host(c, diagrams, d, sizeof(double) * 8 * T);
-    if (!rc && pieces) rc = copy_to_host(c, pieces, d + 8 * T, sizeof(double) * 6 * T);
-  }
-  c->sync();
-  c->dfree(part);
-  for (void* p : out) c->dfree(p);
-  c->dfree(mix);
-  c->dfree(dd);
-  return rc;
+  const Gram gm[5] = {{point_sol, 12, point_sol, 12, 0, T},  // Pn[t][k][l] = <Sp_k, Sp_l>_t
+                      {src1, n1, src2, n2, 0, T},             // G[t][i][j] = <eta1_i, eta2_j>_t
+                      {sol1, n1, sol2, n2, 0, T},             // Fp[t][i][j] = <X1_i, X2_j>_t
+                      {point_sol, 12, sol1, n1, t0, 1},       // A[k][i] = <Sp_k, X1_i>_t0
+                      {sol2, n2, point_sol, 12, 0, T}};       // B[t][j][k] = <X2_j, Sp_k>_t
+  Scratch mem(c);
+  double *out[5], *mix, *d;
+  for (int q = 0; q < 5; ++q) A2A_TRY(mem.get(&out[q], 2 * (size_t)gm[q].nt * gm[q].na * gm[q].nb));
+  A2A_TRY(mem.get(&mix, 6 * (size_t)T * pipi_mixed_chunks(n1)));
+  A2A_TRY(mem.get(&d, 2 * 7 * (size_t)T));  // diagrams [4][T], pieces [3][T]
+  for (int q = 0; q < 5; ++q)
+    A2A_TRY(stoch_ops(c, g, gm[q].nb, gm[q].a, gm[q].b, out[q], 0, gm[q].t_first, gm[q].nt, nullptr, nullptr, gm[q].na));
+  launch_pipi_mixed(T, t0, n1, n2, out[0], out[1], out[2], out[3], out[4], mix, d, d + 8 * T, c->stream);
+  A2A_HIP(c, hipGetLastError());
+  A2A_TRY(copy_to_host(c, diagrams, d, sizeof(double) * 8 * T));
+  if (pieces) A2A_TRY(copy_to_host(c, pieces, d + 8 * T, sizeof(double) * 6 * T));
+  return A2A_OK;
 }
 
 // =========================================================================================
@@ -1605,7 +1588,6 @@ extern "C" int a2a_contract_pion_mom_dev(a2a_ctx* h, const a2a_geom* geom, const
   for (int m0 = 0; m0 < nmom;) {
     MomBatch mb{};
     MomPairs mp{};
-    int nchunk = 1;
     for (; mp.nm < most && m0 + mp.nm < nmom; ++mp.nm) {
       MomBatch more = mb;
       const int ip = batch_phase(g, moms + 3 * (m0 + mp.nm), 1, &more);
@@ -1613,15 +1595,13 @@ extern "C" int a2a_contract_pion_mom_dev(a2a_ctx* h, const a2a_geom* geom, const
       const int ch = by_sc ? stoch_sc_chunks(g, nv, more.nph, n) : stoch_chunks(g, more.nph * na, n, g.T);
       if (mp.nm > 0 && 16.0 * g.T * more.nph * (double)nn * (ch > 1 ? ch + 1 : 1) > MOM_BATCH_BYTES) break;
       mb = more;
-      nchunk = ch;
       mp.ip[mp.nm] = ip;
       mp.im[mp.nm] = im;
     }
     Scratch mem(c);
     const size_t nO = 2 * (size_t)g.T * mb.nph * nn;
-    double *O, *part = nullptr, *ph, *pairs, *dc;
+    double *O, *ph, *pairs, *dc;
     int rc = mem.get(&O, nO);
-    if (!rc && nchunk > 1) rc = mem.get(&part, nO * nchunk);
     if (!rc) rc = mem.get(&ph, 2 * V3 * mb.nph);
     if (!rc) rc = mem.get(&pairs, 2 * (by_time ? (size_t)mp.nm * g.T * g.T : pair_corr_partials(g.T, n, mp.nm)));
     const size_t ncorr = 2 * (size_t)mp.nm * g.T, noff = check ? SC_CHECK_BLOCKS / 2 : 0;  // doubles
@@ -1634,10 +1614,14 @@ extern "C" int a2a_contract_pion_mom_dev(a2a_ctx* h, const a2a_geom* geom, const
     if (rc) return rc;
     const ScCheck sc{src, nv, group, by_time, check ? (int*)(dc + ncorr) : nullptr};
     launch_phases(g, mb, ph, sc, c->stream);
-    if (by_sc)
+    if (by_sc) {
+      int nchunk = stoch_sc_chunks(g, nv, mb.nph, n);
+      double* part;
+      A2A_TRY(chunks_that_fit(c, mem, nO, &nchunk, &part));
       launch_stoch_sc(g, n, nv, mb.nph, group, by_time, src, sol, ph, part, nchunk, O, c->stream);
-    else
-      launch_stoch_ops(g, n, src, sol, part, nchunk, O, c->stream, 1, 0, g.T, ph, drows, mb.nph * na, na);
+    } else {
+      A2A_TRY(stoch_ops(c, g, n, src, sol, O, 1, 0, g.T, ph, drows, mb.nph * na, na));
+    }
     if (by_time)
       launch_pion_mom_rows(g.T, n, na, mb.nph, drows, group, mode, mp, O, pairs, dc, c->stream);
     else
