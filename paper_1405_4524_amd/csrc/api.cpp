@@ -119,7 +119,8 @@ int il_alloc(Ctx* c, Slot* slots, int n, long hv, int nlo, int width) {
 constexpr int IL_REM_MIN = 12;
 
 // ilw: RHS per interleaved group (16, 32 or 48; 0 = the context's option)
-int slots_alloc(Ctx* c, Slot* slots, int n, int prec, long hv, int nblk, int nlo, int nhi, int ilw = 0) {
+int slots_alloc(Ctx* c, Slot* slots, int n, int prec, const OpEntry& op, int nlo, int nhi, int ilw = 0) {
+  const long hv = op.dev.g.hv;
   const bool il = use_interleave(c, prec) && nlo > 0;
   int width = ilw > 0 ? ilw : c->il_width;
   if (width != 16 && width != 32) width = IL_MAX;
@@ -130,7 +131,7 @@ int slots_alloc(Ctx* c, Slot* slots, int n, int prec, long hv, int nblk, int nlo
   }
   int rc = A2A_OK;
   int k = 0;
-  for (; k < n && !rc; ++k) rc = slot_alloc(c, &slots[k], prec, hv, nblk, k < n_il ? 0 : nlo, nhi);
+  for (; k < n && !rc; ++k) rc = slot_alloc(c, &slots[k], prec, hv, k < n_il ? op.partials() : op.nblk, k < n_il ? 0 : nlo, nhi);
   if (!rc && n_il > 0) rc = il_alloc(c, slots, n_il, hv, nlo, width);
   if (rc)
     for (int j = 0; j < k; ++j) slot_free(c, &slots[j]);
@@ -245,7 +246,7 @@ static int solve_batch(Ctx* c, int clover_h, const double* src, int nrhs, double
     s.max_iter = max_iter;
     s.t_submit = t0;
   }
-  rc = slots_alloc(c, slots.data(), nrhs, prec, hv, sv.ops[op].partials(), NVEC_LO, NVEC_HI, tc.il_width);
+  rc = slots_alloc(c, slots.data(), nrhs, prec, sv.ops[op], NVEC_LO, NVEC_HI, tc.il_width);
   if (!rc) {
     std::vector<int> idx;
     for (int i = 0; i < nrhs; ++i) {
@@ -328,7 +329,7 @@ int dslash_core(Ctx* c, int clover_h, double kappa, int opk, int dagger, int pre
     s.src = in + (size_t)i * 24 * V;
     s.sol = out + (size_t)i * 24 * V;
   }
-  rc = slots_alloc(c, slots.data(), nrhs, prec, hv, sv.ops[op].partials(), 5, 0);
+  rc = slots_alloc(c, slots.data(), nrhs, prec, sv.ops[op], 5, 0);
   if (!rc)
     for (auto& s : slots) sv.add_slot(&s);
   if (!rc) rc = sv.rebuild();
@@ -813,7 +814,7 @@ static int stencil_time(Ctx* c, int clover_h, double kappa, int opk, int prec, i
   std::vector<Slot> slots(nrhs);
   int rc = A2A_OK;
   for (int i = 0; i < nrhs; ++i) slots[i].op = op;
-  rc = slots_alloc(c, slots.data(), nrhs, prec, gf->g.hv, sv.ops[op].partials(), 5, 0, tc.il_width);
+  rc = slots_alloc(c, slots.data(), nrhs, prec, sv.ops[op], 5, 0, tc.il_width);
   if (!rc)
     for (auto& s : slots) sv.add_slot(&s);
   if (!rc) rc = sv.rebuild();
@@ -873,7 +874,7 @@ static int ru_time(Ctx* c, int clover_h, double kappa, int prec, int nrhs, int r
   std::vector<Slot> slots(nrhs);
   int rc = A2A_OK;
   for (int i = 0; i < nrhs; ++i) slots[i].op = op;
-  rc = slots_alloc(c, slots.data(), nrhs, prec, gf->g.hv, sv.ops[op].partials(), NVEC_LO, NVEC_HI, il.il_width);
+  rc = slots_alloc(c, slots.data(), nrhs, prec, sv.ops[op], NVEC_LO, NVEC_HI, il.il_width);
   if (!rc)
     for (auto& s : slots) sv.add_slot(&s);
   if (!rc) rc = sv.rebuild();
@@ -1751,7 +1752,7 @@ static int engine_admit(a2a_engine* e, Request* r) {
     s.req = r->ticket;
     s.req_idx = i;
   }
-  rc = slots_alloc(c, r->slots.data(), r->nsrc, r->prec, gf->g.hv, sv->ops[op].partials(), NVEC_LO, NVEC_HI);
+  rc = slots_alloc(c, r->slots.data(), r->nsrc, r->prec, sv->ops[op], NVEC_LO, NVEC_HI);
   if (rc) {
     r->slots.clear();
     return rc;
