@@ -394,6 +394,16 @@ struct Scratch {
   }
 };
 
+// Waits for the stream where a call leaves before its last wait (on an error): what it has queued reads the
+// caller's arrays, host arrays among them, which are the caller's again afterwards.
+struct Pending {
+  Ctx* c;
+  bool done = false;
+  ~Pending() {
+    if (!done) (void)hipStreamSynchronize(c->stream);
+  }
+};
+
 // eta and X on the device: the caller's device arrays, or copies of its host arrays
 int fields_on_device(Ctx* c, Scratch& mem, bool dev, size_t nel, const double** src, const double** sol) {
   if (dev) return A2A_OK;
@@ -1213,6 +1223,7 @@ static int pion_impl(a2a_ctx* h, const a2a_geom* geom, const double* src, const 
   if (geom_to_geo(geom, &g)) return c->fail(A2A_EINVAL, "bad lattice geometry");
   if (n < 1 || (mode == A2A_PION_UNBIASED && n < 2) || (mode != 0 && mode != 1))
     return c->fail(A2A_EINVAL, "need nrhs >= 2 for the unbiased estimator and mode 0 or 1");
+  Pending wait{c};
   Scratch mem(c);
   A2A_TRY(fields_on_device(c, mem, dev, (size_t)n * 24 * 2 * g.hv, &src, &sol));
   // results [corr | O], one copy when O is wanted
@@ -1230,10 +1241,11 @@ static int pion_impl(a2a_ctx* h, const a2a_geom* geom, const double* src, const 
     A2A_TRY(c->sync());
     std::memcpy(corr, c->scal_host, sizeof(double) * 2 * g.T);
     std::memcpy(O_host, c->scal_host + 2 * g.T, sizeof(double) * nO);
-    return A2A_OK;
+  } else {
+    A2A_TRY(copy_to_host(c, corr, out, sizeof(double) * 2 * g.T));
+    if (O_host) A2A_TRY(copy_to_host(c, O_host, O, sizeof(double) * nO));
   }
-  A2A_TRY(copy_to_host(c, corr, out, sizeof(double) * 2 * g.T));
-  if (O_host) A2A_TRY(copy_to_host(c, O_host, O, sizeof(double) * nO));
+  wait.done = true;
   return A2A_OK;
 }
 
@@ -1285,6 +1297,7 @@ static int pipi_impl(a2a_ctx* h, const a2a_geom* geom, const double* src, const 
   Geo g;
   if (geom_to_geo(geom, &g)) return c->fail(A2A_EINVAL, "bad lattice geometry");
   if (n < 4 || n % 4 || n / 4 > 32) return c->fail(A2A_EINVAL, "pi-pi needs nrhs = 4m with 1 <= m <= 32");
+  Pending wait{c};
   Scratch mem(c);
   A2A_TRY(fields_on_device(c, mem, dev, (size_t)n * 24 * 2 * g.hv, &src, &sol));
   double *O, *work, *pairs = nullptr, *out;  // out: diagrams [4][T], loops [T], pion [T]
@@ -1301,6 +1314,7 @@ static int pipi_impl(a2a_ctx* h, const a2a_geom* geom, const double* src, const 
   std::memcpy(diag, hres.data(), sizeof(double) * 8 * g.T);
   if (vac) std::memcpy(vac, hres.data() + 8 * g.T, sizeof(double) * 2 * g.T);
   if (pion) std::memcpy(pion, hres.data() + 10 * g.T, sizeof(double) * 2 * g.T);
+  wait.done = true;
   return A2A_OK;
 }
 
@@ -1444,6 +1458,7 @@ extern "C" int a2a_contract_gram_2pt_dev(a2a_ctx* h, const a2a_geom* geom, const
   A2A_TRY(fill_geo(c, geom, nrhs, t_src, FILL_CONTRACT_MAX_ROWS, &g));
   const int n = nrhs;
   const size_t nn = (size_t)n * n;
+  Pending wait{c};
   Scratch mem(c);
   double *E, *F, *dc;
   A2A_TRY(mem.get(&E, 2 * nn));
@@ -1454,7 +1469,9 @@ extern "C" int a2a_contract_gram_2pt_dev(a2a_ctx* h, const a2a_geom* geom, const
   A2A_TRY(stoch_ops(c, g, n, sol2, sol1, F, 0));
   launch_gram_corr(g.T, n, E, F, dc, c->stream);
   A2A_HIP(c, hipGetLastError());
-  return copy_to_host(c, corr, dc, sizeof(double) * 2 * g.T);
+  A2A_TRY(copy_to_host(c, corr, dc, sizeof(double) * 2 * g.T));
+  wait.done = true;
+  return A2A_OK;
 }
 
 // =========================================================================================
@@ -1498,6 +1515,7 @@ extern "C" int a2a_contract_pipi_mixed_dev(a2a_ctx* h, const a2a_geom* geom, con
                       {sol1, n1, sol2, n2, 0, T},             // Fp[t][i][j] = <X1_i, X2_j>_t
                       {point_sol, 12, sol1, n1, t0, 1},       // A[k][i] = <Sp_k, X1_i>_t0
                       {sol2, n2, point_sol, 12, 0, T}};       // B[t][j][k] = <X2_j, Sp_k>_t
+  Pending wait{c};
   Scratch mem(c);
   double *out[5], *mix, *d;
   for (int q = 0; q < 5; ++q) A2A_TRY(mem.get(&out[q], 2 * (size_t)gm[q].nt * gm[q].na * gm[q].nb));
@@ -1509,6 +1527,7 @@ extern "C" int a2a_contract_pipi_mixed_dev(a2a_ctx* h, const a2a_geom* geom, con
   A2A_HIP(c, hipGetLastError());
   A2A_TRY(copy_to_host(c, diagrams, d, sizeof(double) * 8 * T));
   if (pieces) A2A_TRY(copy_to_host(c, pieces, d + 8 * T, sizeof(double) * 6 * T));
+  wait.done = true;
   return A2A_OK;
 }
 
@@ -1577,6 +1596,7 @@ extern "C" int a2a_contract_pion_mom_dev(a2a_ctx* h, const a2a_geom* geom, const
   bool by_sc = scheme == A2A_DILUTE_SC || scheme == A2A_DILUTE_TSC, check = by_sc;
   // momenta in batches whose operators (and their chunk sums) stay below MOM_BATCH_BYTES, at least one
   constexpr double MOM_BATCH_BYTES = 1e9;
+  Pending wait{c};  // the row table's upload too
   Scratch rowmem(c);
   int* drows = nullptr;
   if (by_time) {
@@ -1642,6 +1662,7 @@ extern "C" int a2a_contract_pion_mom_dev(a2a_ctx* h, const a2a_geom* geom, const
     std::memcpy(corr + 2 * (size_t)m0 * g.T, res.data(), sizeof(double) * ncorr);
     m0 += mp.nm;
   }
+  wait.done = true;
   return A2A_OK;
 }
 
