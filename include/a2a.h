@@ -113,9 +113,10 @@ int a2a_init(a2a_ctx **ctx, int device, size_t hbm_budget_bytes, void *hip_strea
 int a2a_finalize(a2a_ctx *ctx);
 /* Message for the last failed call on ctx (never NULL; empty after success). */
 const char *a2a_last_error(const a2a_ctx *ctx);
-/* Tuning knobs: "rhs_block" (1, 2, 4: RHS per thread in the stencil; unless set, by precision and
- * lattice), "rhs_block64" (1, 2: RHS per thread in the FP64 stencils of set-up, reliable updates
- * and reconstruction; unless set, by lattice), "check_every" (iterations between residual checks), "delta" (reliable-update reduction
+/* Tuning knobs: "rhs_block" (1, 2, 4: RHS per thread in the stencil; 0, the default: by precision
+ * and lattice), "rhs_block64" (1, 2: RHS per thread in the FP64 stencils of set-up, reliable updates
+ * and reconstruction; 0, the default: by lattice), "check_every" (iterations between residual
+ * checks), "delta" (reliable-update reduction
  * factor for FP16 / FP32 storage, default 0.03), "delta_bf16" (the same for BF16, default 0.05),
  * "delta_cgnr" (the same for CGNR with FP16 storage, default 0.1),
  * "delta64" (the same for the FP64-only mode, default 1e-3),

@@ -572,11 +572,11 @@ extern "C" int a2a_set_option(a2a_ctx* h, const char* key, double v) {
   std::string k(key);
   if (k == "rhs_block") {
     int r = (int)v;
-    if (r != 1 && r != 2 && r != 4) return c->fail(A2A_EINVAL, "rhs_block must be 1, 2 or 4");
+    if (v != 0 && r != 1 && r != 2 && r != 4) return c->fail(A2A_EINVAL, "rhs_block must be 0, 1, 2 or 4");
     c->rhs_block = r;
   } else if (k == "rhs_block64") {
     int r = (int)v;
-    if (r != 1 && r != 2) return c->fail(A2A_EINVAL, "rhs_block64 must be 1 or 2");
+    if (v != 0 && r != 1 && r != 2) return c->fail(A2A_EINVAL, "rhs_block64 must be 0, 1 or 2");
     c->rhs_block64 = r;
   } else if (k == "check_every") {
     if (v < 1) return c->fail(A2A_EINVAL, "check_every must be >= 1");

@@ -636,7 +636,7 @@ static void vec_lists(const std::vector<Slot*>& live, const std::vector<OpEntry>
 // Below that one per thread is (16^3x32: 467 against 494 and 235 against 256 us), since twice the blocks
 // hide more latency; 4^3x8 with 4 sources takes 18 us at one per thread, 30 at two and 50 at four.  With
 // 16-bit storage the registers of a second RHS cost more than its links at every size (32^3x64, 12
-// sources: 1880, 2024 and 2336 us for one, two and four).  Results do not depend on the width.
+// sources: 1880, 2024 and 2336 us for one, two and four).  The operator's values do not depend on the width.
 static int rhs_width(int prec, long hv) { return prec <= 1 && hv >= (1L << 18) ? 2 : 1; }
 
 int Solver::rebuild() {
