@@ -70,11 +70,11 @@ struct FillArgs {
   const double* P[2];  // operand pairs: [0] the product to store or S1, [1] S2 (contract mode)
   const double* Q[2];
   long long pk, qk;          // P(m, k) = P[m + k pk], Q(n, k) = Q[n + k qk] (complex elements)
-  long long pz, qz;          // operand offsets per grid.y index (sink timeslice)
+  long long pz;              // contract mode: P's offset per grid.y index (sink timeslice)
   int M, N, K;  // M and N multiples of 96
   double scale;
-  double* out;               // fill mode: C(m, n) at out[z oz + m om + n]
-  long long om, oz;
+  double* out;               // fill mode: C(m, n) at out[m om + n]
+  long long om;
   int dagger;                // store the spin-colour dagger of every 12 x 12 block
   double* partial;           // contract mode: [z][block] complex partials of sum C1 conj(C2)
 };
@@ -82,7 +82,7 @@ struct FillArgs {
 // contractions (fill or Gram matrices), which launch the same for every larger M
 constexpr long long FILL_MAX_ROWS = (1LL << 18) - 1, FILL_CONTRACT_MAX_ROWS = 1LL << 21;
 int fill_blocks(int M, int N);  // blocks and partials of a contraction, per z
-void launch_fill(const FillArgs& a, int nz, hipStream_t s);
+void launch_fill(const FillArgs& a, hipStream_t s);
 void launch_fill_contract(const FillArgs& a, int nz, double* corr, hipStream_t s);
 void launch_pion_corr(int T, int n, const double* O, int mode, double* partial, double* corr, hipStream_t s);
 // work: pipi_work(T, n) complex

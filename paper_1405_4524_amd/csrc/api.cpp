@@ -1407,7 +1407,7 @@ extern "C" int a2a_fill_propagator_dev(a2a_ctx* h, const a2a_geom* geom, const d
   a.out = S;
   a.om = M;
   a.dagger = dagger != 0;
-  launch_fill(a, 1, c->stream);
+  launch_fill(a, c->stream);
   A2A_HIP(c, hipGetLastError());
   return c->sync();
 }

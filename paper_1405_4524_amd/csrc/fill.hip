@@ -8,8 +8,8 @@
 // P of solutions at t and the (12 L^3) x N block Q of sources at t_src; in the canonical
 // [src][t][z][y][x][spin][colour] arrays each (source, timeslice) column is contiguous.  The
 // kernel is generic in the K strides: C(m, n) = scale sum_k P(m, k) conj(Q(n, k)) with
-// P(m, k) = P[m + k pk], Q(n, k) = Q[n + k qk] (complex elements), one product per
-// grid.y index z (operand offsets pz, qz per z).
+// P(m, k) = P[m + k pk], Q(n, k) = Q[n + k qk] (complex elements); the contraction makes one product
+// per grid.y index z (P offset by pz per z).
 //
 // A wave owns a 32 x 32 tile of C (M = 12 X Y Z is a multiple of 96: no tile is ragged) as 2 x 2 tiles of
 // 16 x 16 on v_mfma_f64_16x16x4_f64, four real products per complex tile and K step of 4 (Re += Pr Qr +
@@ -125,9 +125,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
   const int lane = threadIdx.x, idx = lane & 15, kr = lane >> 4;
   const int tiles_n = a.N / E;
   const int m0 = (int)(blockIdx.x / tiles_n) * E, n0 = (int)(blockIdx.x % tiles_n) * E;
-  const long long z = blockIdx.y;
-  const double* const P[1] = {a.P[0] + 2 * (z * a.pz + m0 + idx + kr * a.pk)};
-  const double* const Q[1] = {a.Q[0] + 2 * (z * a.qz + n0 + idx + kr * a.qk)};
+  const double* const P[1] = {a.P[0] + 2 * (m0 + idx + kr * a.pk)};
+  const double* const Q[1] = {a.Q[0] + 2 * (n0 + idx + kr * a.qk)};
   d4v cr[1][NT][NT], ci[1][NT][NT];
   fill_tile<1, NT>(a, kr, P, Q, cr, ci);
   // element q of a 16 x 16 accumulator tile is row 4 q + lane / 16, column lane % 16
@@ -138,7 +137,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
       for (int j = 0; j < NT; ++j)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          stc(a.out + 2 * (z * a.oz + (m0 + 16 * i + 4 * q + kr) * a.om + n0 + 16 * j + idx),
+          stc(a.out + 2 * ((m0 + 16 * i + 4 * q + kr) * a.om + n0 + 16 * j + idx),
               a.scale * cr[0][i][j][q], a.scale * ci[0][i][j][q]);
   } else {
     // (12 u + s, 12 v + s2) -> (12 u + s2, 12 v + s), conjugated
@@ -149,7 +148,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int m = m0 + 16 * i + 4 * q + kr, n = n0 + 16 * j + idx, d = n % 12 - m % 12;
-          stc(a.out + 2 * (z * a.oz + (m + d) * a.om + n - d), a.scale * cr[0][i][j][q], -a.scale * ci[0][i][j][q]);
+          stc(a.out + 2 * ((m + d) * a.om + n - d), a.scale * cr[0][i][j][q], -a.scale * ci[0][i][j][q]);
         }
   }
 }
@@ -170,7 +169,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
       P[p] = a.P[p] + 2 * (z * a.pz + 16 * row + idx + kr * a.pk);
-      Q[p] = a.Q[p] + 2 * (z * a.qz + 16 * col + idx + kr * a.qk);
+      Q[p] = a.Q[p] + 2 * (16 * col + idx + kr * a.qk);
     }
     d4v cr[2][1][1], ci[2][1][1];
     fill_tile<2, 1>(a, kr, P, Q, cr, ci);
@@ -219,8 +218,8 @@ int fill_blocks(int M, int N) {
 }
 
 template <int NT>
-static void launch_fill_t(const FillArgs& a, int nz, hipStream_t s) {
-  const dim3 g((unsigned)((long long)(a.M / (16 * NT)) * (a.N / (16 * NT))), (unsigned)nz);
+static void launch_fill_t(const FillArgs& a, hipStream_t s) {
+  const dim3 g((unsigned)((long long)(a.M / (16 * NT)) * (a.N / (16 * NT))));
   if (a.dagger)
     hipLaunchKernelGGL((k_fill<true, NT>), g, dim3(64), 0, s, a);
   else
@@ -229,11 +228,11 @@ static void launch_fill_t(const FillArgs& a, int nz, hipStream_t s) {
 
 // 2 x 2 tiles from 1024 rows on; below, four times the waves fill more of the chip (768 rows, 128 sources: 36
 // us in 2 x 2 tiles, 34 in single ones; 6144 rows, 1024 sources: 4.7 ms and 5.5)
-void launch_fill(const FillArgs& a, int nz, hipStream_t s) {
+void launch_fill(const FillArgs& a, hipStream_t s) {
   if (a.M >= 1024)
-    launch_fill_t<2>(a, nz, s);
+    launch_fill_t<2>(a, s);
   else
-    launch_fill_t<1>(a, nz, s);
+    launch_fill_t<1>(a, s);
 }
 
 void launch_fill_contract(const FillArgs& a, int nz, double* corr, hipStream_t s) {

@@ -80,16 +80,10 @@ __device__ __forceinline__ uint32_t rot16(uint32_t v) { return (v >> 16) | (v <<
 // Pointers read from the group and operator tables are generic; accesses through them would be
 // FLAT instructions, which count against the LDS counter too and so make every LDS wait also
 // wait for outstanding HBM traffic.  All of these fields point to device global memory.
-typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 typedef const __attribute__((address_space(1))) uint32_t* gptr1;
-typedef const __attribute__((address_space(1))) v2u* gptr2;
 typedef const __attribute__((address_space(1))) v4u* gptr4;
 __device__ __forceinline__ uint32_t gld1(const void* p) { return *(gptr1)p; }
-__device__ __forceinline__ uint2 gld2(const void* p) {
-  const v2u v = *(gptr2)p;
-  return make_uint2(v.x, v.y);
-}
 __device__ __forceinline__ uint4 gld4(const void* p) {
   const v4u v = *(gptr4)p;
   return make_uint4(v.x, v.y, v.z, v.w);
@@ -106,20 +100,6 @@ __device__ __forceinline__ void gst4nt(void* p, const uint4& v) {
   w.z = v.z;
   w.w = v.w;
   __builtin_nontemporal_store(w, (__attribute__((address_space(1))) v4u*)p);
-}
-__device__ __forceinline__ void gst4(void* p, const uint4& v) {
-  v4u w;
-  w.x = v.x;
-  w.y = v.y;
-  w.z = v.z;
-  w.w = v.w;
-  *(__attribute__((address_space(1))) v4u*)p = w;
-}
-__device__ __forceinline__ void gst2(void* p, const uint2& v) {
-  v2u w;
-  w.x = v.x;
-  w.y = v.y;
-  *(__attribute__((address_space(1))) v2u*)p = w;
 }
 
 // (1 + sg gamma_mu)[s][t] in the chiral basis as a unit complex (re, im), entries in {-1, 0, 1}.
@@ -213,7 +193,9 @@ struct SiteIn {
 // compact cells of bricks 3557 (its reads and writes alone take 2.6 ms at the rate of a
 // copy); 24^3x48, 32 RHS: 954, 933, 910, 895; 16^3x32, 16 RHS: 114, 114, 113, 111.
 //
-// One tile (DEPTH 2: requests two sites ahead) and two tiles fit three waves per SIMD, three tiles two; two
+// Registers: one tile (DEPTH 2: requests two sites ahead) takes 124-152 of the 168 that three waves per SIMD
+// leave a wave, two tiles 148-162, three 184-232 of the 256 of two waves.  With a reduction two tiles do not
+// quite fit: the compiler spills 2 (RED_OMEGA), 7 (RED_ALPHA, EPI 3) or 36 (RED_ALPHA, EPI 1) of them.  Two
 // tiles two sites ahead at two waves take 86 us for 73 at 12^3x24 and the same on larger lattices.
 template <class P, int EPI, int RED, int NT>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(NT == 3 ? 2 : 3))) void k_hop_mfma(HopMArgs a) {
