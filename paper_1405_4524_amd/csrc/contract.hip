@@ -433,8 +433,10 @@ void launch_phases(const Geo& g, const MomBatch& m, double* f, const ScCheck& ch
 // wave per component (12 per block), 16 NA virtual rows (phase, noise vector) x 32 columns; the block
 // stages 4 sites of its columns in LDS (768-byte runs), every wave takes its component from
 // there as the K step's four sites.  8^3x16, 768 sources, 11 phases: the dense products over zeros took
-// 13.9 ms, this 0.72 (40 TFLOP/s of matrix products; 384 blocks of one per CU are one and a half rounds,
-// and more, shorter ones cost as much in repeated rows or partial sums).
+// 13.9 ms, this 0.72 (40 TFLOP/s of matrix products, padding counted).  Neither memory (1.6 GB fetched) nor the
+// matrix cores (53% busy) bound it: a CU holds one block, whose waves stage, meet at a barrier and multiply
+// in turn, and 384 blocks are one and a half rounds (more, shorter ones cost as much in repeated rows or
+// partial sums).
 constexpr int SC_SITES = 4;                 // sites per stage (one K step)
 constexpr int SC_COLS = 2;                  // column tiles of a block
 constexpr int SC_ROW = SC_SITES * 12 + 1;   // complex per staged column (padded: 16 columns, distinct banks)

@@ -180,8 +180,9 @@ struct SiteIn {
 // (the whole x row, then y, z, t extents), so that most neighbours of a block's sites are sites of the same
 // block.  A wave builds a site's matrix and applies it to every tile of the group.
 //
-// What bounds it: gathered lines that miss the CU's vector L1.  At 48 RHS a CU has about 68 128-byte requests
-// to its L2 in flight, 490 cycles each, while address, matrix and LDS units idle half the time, so the count
+// What bounds it: gathered lines that miss the CU's vector L1.  At 48 RHS a CU has about 85 128-byte requests
+// to its L2 in flight, 570 cycles each, its address units are busy or waiting 93% of the time and the matrix
+// cores 24% (32^3x64, inverse epilogue; 68 requests of 490 cycles with eight gathers a site), so the count
 // of gathered lines sets the time (with every gather in one L2-resident line set the pair below took 2.9 ms).
 // A wave therefore sweeps pairs of output sites in adjacent y rows along x: each new pair needs one new
 // input per row, the inputs behind them and each other's row stay in registers, and a site gathers six
